@@ -529,6 +529,303 @@ __global__ __launch_bounds__(256) void k_arnoldi_finish(const double2 *__restric
     }
 }
 
+// ---- batches of 2 .. 512 right-hand sides with one basis vector per rhs ----
+// A vector is a flat array of rows (site, component) of N elements.  A
+// workgroup takes R consecutive rows at a time, R N <= 512 threads, thread t
+// element t of them: its right-hand side t % N never changes, and whatever N
+// is, a wavefront reads one contiguous run (a (site, rhs) tile reads 64-byte
+// pieces at N = 12 and leaves a quarter of its lanes idle).  Bound by HBM: w is
+// read once for up to 16 (FP64: 8) basis vectors, all loads of a row group
+// issued together.
+struct FlatTiling {
+    int R;         // rows per workgroup step
+    int threads;   // R N rounded up to whole wavefronts
+    int NB;        // workgroups per group of basis vectors
+};
+constexpr int kFlatMaxN = 512;
+constexpr size_t kFlatCached = (size_t)640 << 20;   // operands up to here: mostly cached (see blas_multi_dot)
+
+// The flat kernels, or the (site, rhs) tiles?  Tiles read whole lines where 64
+// right-hand sides fill a wavefront: there the dot product gains only from
+// reading w once for more than the tiles' four vectors (24^4 x 64 FP16S: four
+// vectors 1,038 us in tiles and 1,117 us flat, ten 2,805 us and 2,279 us), the
+// update nothing (8^4 x 64, ten vectors: 47 us and 53 us).  Elsewhere the flat
+// kernels win once a vector is too large for its launch to be mere latency
+// (ten vectors and FP32, N = 12: 8^4, 4.7 MB, 15.8 us in tiles and 17.0 us
+// flat; 12^4, 24 MB, 87.7 us and 53.5 us; 16^4, 75 MB, 280 us and 160 us).
+bool use_flat(const mpmc_ctx *ctx, int N, int nv, int prec, bool dot) {
+    if (N < 2 || N > kFlatMaxN) return false;
+    if (N % 64 == 0) return dot && nv > JB;
+    return vec_bytes(ctx, N, prec) >= (size_t)10000000;
+}
+
+// R near 256 threads' worth, moved to where the fewest lanes of the last
+// wavefront idle.  Every workgroup is resident at once, `waves` wavefronts per
+// compute unit: a partial second round would run with most of the chip idle
+// (16^4 x 12, ten vectors: 161 us with 1,365 workgroups of three wavefronts,
+// of which 1,280 fit, 149 us with 1,280).
+FlatTiling flat_tiling(const mpmc_ctx *ctx, int N, int groups, int waves = 16) {
+    FlatTiling t{1, (N + 63) / 64 * 64, 1};
+    for (int R = 1; R * N <= (N <= 128 ? 256 : kFlatMaxN); ++R) {
+        const int th = (R * N + 63) / 64 * 64;
+        if ((long)R * N * t.threads >= (long)t.R * N * th) {
+            t.R = R;
+            t.threads = th;
+        }
+    }
+    const long nrb = (ctx->V * 12 + t.R - 1) / t.R;
+    const int per_cu = waves * 64 / t.threads;
+    long nb = (long)ctx->num_cu * (per_cu > 0 ? per_cu : 1) / groups;
+    if (nb < 64) nb = 64;
+    const long steps = (nrb + nb - 1) / nb;   // of the busiest workgroup: as few workgroups as it allows
+    t.NB = (int)((nrb + steps - 1) / steps);
+    return t;
+}
+
+// Sums of v[0 .. n-1] over the R threads of each right-hand side (threads r,
+// r + N, ...), in a fixed order; the results are thread r's (r < N).  Four at a
+// time: the barriers of one sum after the other show on a small lattice
+// (6^4 x 12, twelve vectors: 19.2 us one by one, 16.1 us in fours).
+constexpr int kFlatSums = 4;
+template <int n>
+__device__ __forceinline__ void flat_sums(cpx<double> (&v)[n], double2 (*red)[512], int N, int R, int rr, bool live) {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int q0 = 0; q0 < n; q0 += kFlatSums) {
+        if (q0) __syncthreads();
+        if (live) {
+#pragma unroll
+            for (int q = 0; q < kFlatSums; ++q)
+                if (q0 + q < n) red[q][t] = make_double2(v[q0 + q].re, v[q0 + q].im);
+        }
+        __syncthreads();
+        for (int h = R; h > 1;) {
+            const int half = (h + 1) / 2;
+            if (live && rr < h - half) {
+#pragma unroll
+                for (int q = 0; q < kFlatSums; ++q)
+                    if (q0 + q < n) {
+                        red[q][t].x += red[q][t + half * N].x;
+                        red[q][t].y += red[q][t + half * N].y;
+                    }
+            }
+            __syncthreads();
+            h = half;
+        }
+        if (live && rr == 0) {
+#pragma unroll
+            for (int q = 0; q < kFlatSums; ++q)
+                if (q0 + q < n) v[q0 + q] = mk(red[q][t].x, red[q][t].y);
+        }
+    }
+}
+
+// partial[j][blk][r] = sum over the block's rows of conj(V_j) Theta w for the
+// JG basis vectors from blockIdx.y JG on.
+template <int P, int JG>
+__global__ __launch_bounds__(512) void k_multidot_flat(const void *__restrict__ Vb, size_t vstride_b, int nv,
+                                                       const void *__restrict__ w, int N, int R, long rows, int theta,
+                                                       double2 *__restrict__ partial, int NB) {
+    using E = typename std::conditional<P == MPMC_FP64, double2, float2>::type;
+    constexpr int U = JG <= 2 ? (P == MPMC_FP32 ? 4 : 2) : (JG <= 6 && P == MPMC_FP32 ? 2 : 1);   // row groups in flight
+    __shared__ double2 red[JG < kFlatSums ? JG : kFlatSums][512];
+    const int T = R * N, t = threadIdx.x, rr = t / N;
+    const bool live = t < T;
+    const int j0 = blockIdx.y * JG;
+    cpx<double> acc[JG];
+#pragma unroll
+    for (int q = 0; q < JG; ++q) acc[q] = mk(0.0, 0.0);
+    // rows rb R .. rb R + R - 1; the group's offset is uniform, the lane's is t
+    auto group = [&](auto NU, long rb) {
+        constexpr int nu = decltype(NU)::value;
+        E wv[nu], vv[nu][JG];
+#pragma unroll
+        for (int u = 0; u < nu; ++u) {
+            const size_t off = (size_t)(rb + (long)u * NB) * T * sizeof(E);
+            wv[u] = reinterpret_cast<const E *>((const char *)w + off)[t];
+#pragma unroll
+            for (int q = 0; q < JG; ++q) {   // past the last vector: read again, not used
+                const int j = j0 + q < nv ? j0 + q : nv - 1;
+                vv[u][q] = reinterpret_cast<const E *>((const char *)Vb + (size_t)j * vstride_b + off)[t];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < nu; ++u) {
+            double sg = 1.0;
+            if (theta && ((rb + (long)u * NB) * R + rr) % 12 >= 6) sg = -1.0;
+            const cpx<double> wd = mk(sg * (double)wv[u].x, sg * (double)wv[u].y);
+#pragma unroll
+            for (int q = 0; q < JG; ++q)
+                acc[q] = acc[q] + conjmul(mk((double)vv[u][q].x, (double)vv[u][q].y), wd);
+        }
+    };
+    if (live) {
+        const long full = rows / R;   // whole row groups
+        long rb = blockIdx.x;
+        for (; rb + (long)(U - 1) * NB < full; rb += (long)U * NB) group(std::integral_constant<int, U>(), rb);
+        for (; rb * R + rr < rows; rb += NB) group(std::integral_constant<int, 1>(), rb);
+    }
+    flat_sums(acc, red, N, R, rr, live);
+    if (live && rr == 0) {
+#pragma unroll
+        for (int q = 0; q < JG; ++q)
+            if (j0 + q < nv)
+                partial[((long)(j0 + q) * NB + blockIdx.x) * N + t] = make_double2(acc[q].re, acc[q].im);
+    }
+}
+
+// The same for an FP16S basis and FP32 w: thread = (site, rhs) pair, R sites at
+// a time, four components of all JG vectors in flight, so w is read once for
+// up to 12 vectors (4 in a (site, rhs) tile with every component in registers).
+template <int JG>
+__global__ __launch_bounds__(512) void k_multidot_flat_h(const void *__restrict__ Vb, size_t vstride_b,
+                                                         size_t vscale_off, int nv, const void *__restrict__ w, int N,
+                                                         int R, long V, double2 *__restrict__ partial, int NB) {
+    constexpr int KC = 4;
+    __shared__ double2 red[JG < kFlatSums ? JG : kFlatSums][512];
+    const int T = R * N, t = threadIdx.x, rr = t / N, r = t - rr * N;
+    const bool live = t < T;
+    const int j0 = blockIdx.y * JG;
+    cpx<double> acc[JG];
+#pragma unroll
+    for (int q = 0; q < JG; ++q) acc[q] = mk(0.0, 0.0);
+    const uint32_t lane = (uint32_t)rr * 12u * (uint32_t)N + (uint32_t)r;   // the pair's component 0 within the sites
+    if (live) {
+        for (long sb = blockIdx.x; sb * R + rr < V; sb += NB) {
+            const size_t base = (size_t)sb * T;   // uniform: first pair of the sites
+            float sc[JG];
+#pragma unroll
+            for (int q = 0; q < JG; ++q) {
+                const int j = j0 + q < nv ? j0 + q : nv - 1;
+                sc[q] = (reinterpret_cast<const float *>((const char *)Vb + (size_t)j * vstride_b + vscale_off) + base)[t];
+            }
+#pragma unroll 1   // unrolled, all twelve components' loads move up and spill
+            for (int kc = 0; kc < 12; kc += KC) {
+                float2 wv[KC];
+                __half2 vv[KC][JG];
+#pragma unroll
+                for (int k = 0; k < KC; ++k) {
+                    const size_t row = base * 12 + (size_t)(kc + k) * N;
+                    wv[k] = (reinterpret_cast<const float2 *>(w) + row)[lane];
+#pragma unroll
+                    for (int q = 0; q < JG; ++q) {
+                        const int j = j0 + q < nv ? j0 + q : nv - 1;
+                        vv[k][q] = (reinterpret_cast<const __half2 *>((const char *)Vb + (size_t)j * vstride_b) + row)[lane];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < KC; ++k) {
+                    const cpx<double> wd = mk((double)wv[k].x, (double)wv[k].y);
+#pragma unroll
+                    for (int q = 0; q < JG; ++q) {
+                        const float2 f = __half22float2(vv[k][q]);
+                        acc[q] = acc[q] + conjmul(mk((double)(f.x * sc[q]), (double)(f.y * sc[q])), wd);
+                    }
+                }
+            }
+        }
+    }
+    flat_sums(acc, red, N, R, rr, live);
+    if (live && rr == 0) {
+#pragma unroll
+        for (int q = 0; q < JG; ++q)
+            if (j0 + q < nv)
+                partial[((long)(j0 + q) * NB + blockIdx.x) * N + t] = make_double2(acc[q].re, acc[q].im);
+    }
+}
+
+// w += sign * sum_j h[j*ldh + r] V_j; optional partial[blk][r] = sum |w|^2.
+// NV > 0: exactly NV vectors, coefficients in registers throughout; NV = 0: any
+// number, eight at a time with their coefficients read again per row group.
+template <int P, int NV>
+__global__ __launch_bounds__(512) void k_multiaxpy_flat(const void *__restrict__ Vb, size_t vstride_b, int nv,
+                                                        void *__restrict__ w, int N, int R, long rows,
+                                                        const double2 *__restrict__ h, int ldh, double sign,
+                                                        double2 *__restrict__ partial, int NB) {
+    using T = typename Store<P>::real;
+    using E = typename std::conditional<P == MPMC_FP64, double2, float2>::type;
+    constexpr int C = NV > 0 ? NV : 8;
+    constexpr int U = C <= 2 ? 4 : (C <= 8 && P == MPMC_FP32 ? 2 : 1);
+    __shared__ double2 red[1][512];
+    const int Tn = R * N, t = threadIdx.x, rr = t / N, r = t - rr * N;
+    const bool live = t < Tn;
+    double nrm = 0;
+    cpx<T> c[C];
+    auto coefs = [&](int j0) {
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            const int j = NV > 0 || j0 + q < nv ? j0 + q : nv - 1;
+            const double2 hj = h[(long)j * ldh + r];
+            c[q] = mk((T)(sign * hj.x), (T)(sign * hj.y));
+        }
+    };
+    auto group = [&](auto NU, long rb) {
+        constexpr int nu = decltype(NU)::value;
+        cpx<T> acc[nu];
+        auto chunk = [&](int j0) {
+            E vv[nu][C];
+#pragma unroll
+            for (int u = 0; u < nu; ++u) {
+                const size_t off = (size_t)(rb + (long)u * NB) * Tn * sizeof(E);
+#pragma unroll
+                for (int q = 0; q < C; ++q) {
+                    const int j = NV > 0 || j0 + q < nv ? j0 + q : nv - 1;
+                    vv[u][q] = reinterpret_cast<const E *>((const char *)Vb + (size_t)j * vstride_b + off)[t];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q)
+                if (NV > 0 || j0 + q < nv)
+#pragma unroll
+                    for (int u = 0; u < nu; ++u) acc[u] = acc[u] + c[q] * mk((T)vv[u][q].x, (T)vv[u][q].y);
+        };
+#pragma unroll
+        for (int u = 0; u < nu; ++u) {
+            const E v = reinterpret_cast<const E *>((const char *)w + (size_t)(rb + (long)u * NB) * Tn * sizeof(E))[t];
+            acc[u] = mk((T)v.x, (T)v.y);
+        }
+        if constexpr (NV > 0) {
+            chunk(0);
+        } else {
+            for (int j0 = 0; j0 < nv; j0 += C) {
+                coefs(j0);
+                chunk(j0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < nu; ++u) {
+            E o;
+            o.x = acc[u].re;
+            o.y = acc[u].im;
+            reinterpret_cast<E *>((char *)w + (size_t)(rb + (long)u * NB) * Tn * sizeof(E))[t] = o;
+            nrm += (double)acc[u].re * acc[u].re + (double)acc[u].im * acc[u].im;
+        }
+    };
+    if (live) {
+        if constexpr (NV > 0) coefs(0);
+        const long full = rows / R;
+        long rb = blockIdx.x;
+        for (; rb + (long)(U - 1) * NB < full; rb += (long)U * NB) group(std::integral_constant<int, U>(), rb);
+        for (; rb * R + rr < rows; rb += NB) group(std::integral_constant<int, 1>(), rb);
+    }
+    if (!partial) return;
+    cpx<double> v[1] = {mk(nrm, 0.0)};
+    flat_sums(v, red, N, R, rr, live);
+    if (live && rr == 0) partial[(long)blockIdx.x * N + r] = make_double2(v[0].re, 0.0);
+}
+
+// f(std::integral_constant<int, n>()) for the run-time n in 1 .. MAX
+template <int MAX, typename F>
+void with_count(int n, F &&f) {
+    if constexpr (MAX > 1) {
+        if (n < MAX) {
+            with_count<MAX - 1>(n, f);
+            return;
+        }
+    }
+    f(std::integral_constant<int, MAX>());
+}
+
 int nb_single(const mpmc_ctx *ctx, long n, int groups) {
     long nb = (long)ctx->num_cu * 8 / (groups > 0 ? groups : 1);
     const long maxnb = (n + 255) / 256;
@@ -565,6 +862,34 @@ int blas_multi_dot(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv, 
         HIP_OR_RET(ctx, hipGetLastError());
         return MPMC_OK;
     }
+    if (vN == nrhs && (prec == MPMC_FP64 || prec == MPMC_FP32) && use_flat(ctx, nrhs, nv, prec, true)) {
+        // basis vectors per group, evenly filled: as many as the registers allow,
+        // since each group reads w again (16^4 x 64 FP32, 16 vectors: 1,193 us
+        // in one group, 1,290 us in four); four where much of it stays in the
+        // 256 MB memory-side cache and wavefronts in flight count for more
+        // (8^4 x 64, 12 vectors: 66 us in three groups, 75 us in one)
+        const size_t vb = (size_t)ctx->n * nrhs * (prec == MPMC_FP64 ? 16 : 8);
+        const int most = (nv + 1) * vb <= kFlatCached ? 4 : prec == MPMC_FP64 ? 8 : 16;
+        const int ng = (nv + most - 1) / most, per = (nv + ng - 1) / ng;
+        const FlatTiling t = flat_tiling(ctx, nrhs, ng, per > 12 ? 12 : 16);
+        double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)nv * t.NB * nrhs * sizeof(double2));
+        if (!part) return MPMC_ENOMEM;
+        const dim3 grd(t.NB, ng);
+        if (prec == MPMC_FP64)
+            with_count<8>(per, [&](auto JG) {
+                k_multidot_flat<MPMC_FP64, decltype(JG)::value><<<grd, t.threads, 0, ctx->stream>>>(
+                    Vb, (size_t)vstride * 16, nv, w, nrhs, t.R, ctx->V * 12, theta, part, t.NB);
+            });
+        else
+            with_count<16>(per, [&](auto JG) {
+                k_multidot_flat<MPMC_FP32, decltype(JG)::value><<<grd, t.threads, 0, ctx->stream>>>(
+                    Vb, (size_t)vstride * 8, nv, w, nrhs, t.R, ctx->V * 12, theta, part, t.NB);
+            });
+        HIP_OR_RET(ctx, hipGetLastError());
+        k_reduce<<<nv * nrhs, 256, 0, ctx->stream>>>(part, t.NB, nrhs, (double2 *)h_dev, accumulate, 0);
+        HIP_OR_RET(ctx, hipGetLastError());
+        return MPMC_OK;
+    }
     Tiling t = tiling(ctx, nrhs, groups);
     double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)nv * t.NB * nrhs * sizeof(double2));
     if (!part) return MPMC_ENOMEM;
@@ -585,6 +910,21 @@ int blas_multi_dot(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv, 
 int blas_multi_dot_h(mpmc_ctx *ctx, const void *Vb, size_t vstride_b, int nv, const void *w, int nrhs,
                      double *h_dev, int accumulate) {
     if (nv <= 0) return MPMC_OK;
+    if (use_flat(ctx, nrhs, nv, MPMC_FP16S, true)) {
+        const int most = nv * vstride_b + vec_bytes(ctx, nrhs, MPMC_FP32) <= kFlatCached ? 4 : 12;   // as blas_multi_dot
+        const int ng = (nv + most - 1) / most, per = (nv + ng - 1) / ng;
+        const FlatTiling t = flat_tiling(ctx, nrhs, ng, per > 10 ? 12 : 16);
+        double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)nv * t.NB * nrhs * sizeof(double2));
+        if (!part) return MPMC_ENOMEM;
+        with_count<12>(per, [&](auto JG) {
+            k_multidot_flat_h<decltype(JG)::value><<<dim3(t.NB, ng), t.threads, 0, ctx->stream>>>(
+                Vb, vstride_b, fp16s_scale_offset(ctx, nrhs), nv, w, nrhs, t.R, ctx->V, part, t.NB);
+        });
+        HIP_OR_RET(ctx, hipGetLastError());
+        k_reduce<<<nv * nrhs, 256, 0, ctx->stream>>>(part, t.NB, nrhs, (double2 *)h_dev, accumulate, 0);
+        HIP_OR_RET(ctx, hipGetLastError());
+        return MPMC_OK;
+    }
     const int groups = (nv + JB - 1) / JB;
     Tiling t = tiling(ctx, nrhs, groups);
     double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)nv * t.NB * nrhs * sizeof(double2));
@@ -645,6 +985,34 @@ int blas_multi_axpy(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv,
         RET_IF(rc);
         if (norm2_dev) {
             k_reduce<<<1, 256, 0, ctx->stream>>>(part, NB, 1, (double2 *)norm2_dev, 0, 1);
+            HIP_OR_RET(ctx, hipGetLastError());
+        }
+        return MPMC_OK;
+    }
+    if (vN == nrhs && nv > 0 && (prec == MPMC_FP64 || prec == MPMC_FP32) && use_flat(ctx, nrhs, nv, prec, false)) {
+        const FlatTiling t = flat_tiling(ctx, nrhs, 1);
+        double2 *part = nullptr;
+        if (norm2_dev) {
+            part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)t.NB * nrhs * sizeof(double2));
+            if (!part) return MPMC_ENOMEM;
+        }
+        const size_t vs = (size_t)vstride * (prec == MPMC_FP64 ? 16 : 8);
+        auto launch = [&](auto P, auto NV) {
+            k_multiaxpy_flat<decltype(P)::value, decltype(NV)::value><<<t.NB, t.threads, 0, ctx->stream>>>(
+                Vb, vs, nv, w, nrhs, t.R, ctx->V * 12, (const double2 *)h_dev, ldh, sign, part, t.NB);
+        };
+        if (prec == MPMC_FP64) {
+            const std::integral_constant<int, MPMC_FP64> P;
+            if (nv <= 12) with_count<12>(nv, [&](auto NV) { launch(P, NV); });
+            else launch(P, std::integral_constant<int, 0>());
+        } else {
+            const std::integral_constant<int, MPMC_FP32> P;
+            if (nv <= 24) with_count<24>(nv, [&](auto NV) { launch(P, NV); });
+            else launch(P, std::integral_constant<int, 0>());
+        }
+        HIP_OR_RET(ctx, hipGetLastError());
+        if (norm2_dev) {
+            k_reduce<<<nrhs, 256, 0, ctx->stream>>>(part, t.NB, nrhs, (double2 *)norm2_dev, 0, 1);
             HIP_OR_RET(ctx, hipGetLastError());
         }
         return MPMC_OK;
