@@ -46,6 +46,7 @@ constexpr int FIELDS[4] = {1, 2, 2, 1};
 constexpr int LAYER_OFF[4] = {0, 576, 1728, 2304};   // real parameters before layer l
 constexpr int TABLE_ELEMS = NPATH * 64 * 4;          // bf16 A-operand table of one layer op
 constexpr int WGRAD_BLOCKS = 1024;                   // blocks (4 wavefronts each) of the weight-gradient grid
+constexpr unsigned LOSS_BLOCKS = 2048;               // blocks of the loss grid
 
 __device__ __forceinline__ short to_bf16(float f) {
     return __builtin_bit_cast(short, (__bf16)f);
@@ -242,28 +243,90 @@ __global__ __launch_bounds__(256) void k_net_layer(const float2 *__restrict__ in
     }
 }
 
+// Four consecutive right-hand sides r0 .. r0 + 3 of a component row (row:
+// channel 0's, wave-uniform; lrow: the lane's channel row and first right-hand
+// side as an element offset), as the operands of a lane that computes the real
+// (part 0: p = re, q = -im) or the imaginary part (part 1: p = im, q = re) of
+// a product with them.  VEC (N % 4 == 0, 16-byte aligned rows): the two lanes
+// of a channel load two right-hand sides each and exchange them (DPP), half
+// the loads.  All loads are unconditional (under a condition the compiler
+// splits them into single dwords, each behind a branch): past N the row's last
+// right-hand sides again.
+__device__ __forceinline__ float pair_swap(float v) {   // the value of the other lane of a pair
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, true));
+}
+template <bool VEC>
+struct Rhs4 {
+    float4 v;        // VEC: the lane's two right-hand sides
+    float2 e[4];     // else all four
+    __device__ __forceinline__ void load(const float2 *row, uint32_t lrow, int rl, int N, int part) {
+        if constexpr (VEC) {
+            v = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(row) + (lrow + 2u * part) * 8u);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                e[j] = *reinterpret_cast<const float2 *>(reinterpret_cast<const char *>(row) +
+                                                         (lrow + (uint32_t)(rl + j < N ? j : N - 1 - rl)) * 8u);
+        }
+    }
+    __device__ __forceinline__ void operands(int part, float (&p)[4], float (&q)[4]) const {
+        if constexpr (VEC) {
+            const float sx = pair_swap(v.x), sy = pair_swap(v.y), sz = pair_swap(v.z), sw = pair_swap(v.w);
+            p[0] = part ? sy : v.x;   // lane 0 holds right-hand sides 0 and 1, lane 1 holds 2 and 3
+            p[1] = part ? sw : v.z;
+            p[2] = part ? v.y : sx;
+            p[3] = part ? v.w : sz;
+            q[0] = part ? sx : -v.y;
+            q[1] = part ? sz : -v.w;
+            q[2] = part ? v.x : -sy;
+            q[3] = part ? v.z : -sw;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                p[j] = part ? e[j].y : e[j].x;
+                q[j] = part ? e[j].x : -e[j].y;
+            }
+        }
+    }
+};
+
 // Weight gradient of one layer: P_p[i][b] = sum_{x, rhs, c} g_i(x, rhs, c) t_{p,b}(x, rhs, c)
 // with i = 2o + ro over the output channels (g = dL/d out^*) and b = 2 ci + ri
 // over the path's transported input channels.  Each wavefront sums its units
 // (site, 16 rhs) in registers; the four wavefronts of a block are added in LDS
 // and the block writes partial[block][p][lane*4 + r] = P_p[4 (lane/16) + r][lane % 16].
-template <int FIN, int FOUT>
-__global__ __launch_bounds__(256) void k_net_wgrad(const float2 *__restrict__ a_in, const float2 *__restrict__ gout,
-                                                   const float2 *__restrict__ links, const int *__restrict__ nbr,
-                                                   float *__restrict__ partial, int N, int nrb, unsigned nunits,
-                                                   const int *__restrict__ order) {
-    // transposition buffer [wave][colour][b][rhs] (bf16), reused for the block sum
+// Both MFMA operands want a lane to hold one channel's four right-hand sides
+// 4g .. 4g + 3, so that is what a lane transports: channel b = lane % 16, the
+// real or the imaginary part (p = x or y, q = -y or x: one form of FMA chain
+// for both), and nothing is transposed.  Right-hand sides past N count zero
+// through the g operand; channels past the layer's repeat valid ones, and
+// their rows and columns of P are not used.  All nine paths are unrolled: the
+// accumulators stay in registers (indexed by a run-time path they lived in
+// scratch).  Bound by the FMA chains (72 of ~110 VALU instructions a path) and
+// the L2; 16^4 x 16, 2 -> 2 fields: 572 us with lanes owning right-hand sides,
+// the transposition through LDS and the accumulators in scratch; 360 us with
+// four right-hand sides loaded by each lane (both lanes of a channel the same
+// ones), 291 us with the halves exchanged, 190 us with the next path's loads in
+// flight as well.
+template <int FIN, int FOUT, bool VEC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_net_wgrad(
+    const float2 *__restrict__ a_in, const float2 *__restrict__ gout, const float2 *__restrict__ links,
+    const int *__restrict__ nbr, float *__restrict__ partial, int N, int nrb, unsigned nunits,
+    const int *__restrict__ order) {
     __shared__ float red[4][NPATH * 256];
-    short(*lds)[3][16][16] = reinterpret_cast<short(*)[3][16][16]>(&red[0][0]);
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
-    const unsigned wave = blockIdx.x * 4u + wv;
+    // each XCD takes a contiguous eighth of the blocks, whose units in a round
+    // are consecutive sites of the blocked order: their neighbours share an L2
+    // (the units of a block and its partial stay the same)
+    const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+    const unsigned wave = tile * 4u + wv;
     const unsigned nwaves = gridDim.x * 4u;
-    const int n = lane & 15, g = lane >> 4;
-    const int f = g >> 1, s0 = 2 * (g & 1);
+    const int g = lane >> 4;
     constexpr int CIN = 12 * FIN, COUT = 12 * FOUT;
-    // output-gradient operand: row i = lane % 16 -> channel o = i/2, part i&1
-    const int oi = (lane & 15) >> 1, opart = lane & 1;
+    // row i = b = lane % 16: channel i/2 = field*4 + spin, part i & 1
+    const int ch = (lane & 15) >> 1, part = lane & 1;
+    const int arow = ((ch >> 2) & (FIN - 1)) * 12 + (ch & 3) * 3, grow = ((ch >> 2) & (FOUT - 1)) * 12 + (ch & 3) * 3;
 
     f32x4 acc[NPATH];
 #pragma unroll
@@ -274,83 +337,101 @@ __global__ __launch_bounds__(256) void k_net_wgrad(const float2 *__restrict__ a_
         const unsigned q = u / (unsigned)nrb;
         const long site = uni(order[q]);   // blocked site order, as in k_net_layer
         const int rb = (int)(u - q * (unsigned)nrb);
-        // A operands: g_i at rhs rb*16 + 4g + j, one per colour
+        const int r0 = rb * 16 + 4 * g;
+        // first right-hand side to load: past N (ragged last block) valid ones again
+        const int rl = VEC ? (r0 < N ? r0 : N - 4) : (r0 < N ? r0 : N - 1);
+        const uint32_t la = (uint32_t)(arow * N + rl), lg = (uint32_t)(grow * N + rl);
+        // A operands: g_i at the lane's right-hand sides, one per colour
         bf16x4 Ag[3];
-        {
-            const bool ok = oi < 4 * FOUT;
-            const int fo = oi >> 2, so = oi & 3;
-            const float2 *gp = gout + (site * COUT + fo * 12 + so * 3) * (long)N;
+        const float2 *gp = gout + site * (long)COUT * N;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                float v[4];
+        for (int c = 0; c < 3; ++c) {
+            Rhs4<VEC> e;
+            e.load(gp + c * (long)N, lg, rl, N, part);
+            float v[4], unused[4];
+            e.operands(part, v, unused);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = rb * 16 + 4 * g + j;
-                    float2 w = (ok && r < N) ? gp[c * (long)N + r] : make_float2(0.f, 0.f);
-                    v[j] = opart ? w.y : w.x;
-                }
-                Ag[c] = pack4(v[0], v[1], v[2], v[3]);
-            }
+            for (int j = 0; j < 4; ++j)
+                if (r0 + j >= N) v[j] = 0.f;
+            Ag[c] = pack4(v[0], v[1], v[2], v[3]);
         }
-        const int rhs = rb * 16 + n;
-        const bool act = rhs < N && f < FIN;
         const int nbw = nbr[site * 8 + (lane & 7)];
-#pragma unroll 1
+        // the next path's spinors are in flight while this one's compute
+        Rhs4<VEC> raw[2][3];
+        auto fetch = [&](int p) {
+            const float2 *src = a_in + path_src(nbw, links, site, p).src * (long)CIN * N;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) raw[p & 1][d].load(src + d * (long)N, la, rl, N, part);
+        };
+        fetch(0);
+#pragma unroll
         for (int p = 0; p < NPATH; ++p) {
+            if (p + 1 < NPATH) fetch(p + 1);
+            __builtin_amdgcn_sched_barrier(0);
             const PathSrc ps = path_src(nbw, links, site, p);
-            float2 a[2][3];
-            const float2 *src = a_in + (ps.src * CIN + f * 12 + s0 * 3) * (long)N + rhs;
+            float x[3][4], y[3][4];
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) a[s][c] = act ? src[(s * 3 + c) * (long)N] : make_float2(0.f, 0.f);
-            float2 t[2][3];
-            transport(ps, a, t);
-            // lane (rhs n, group g) owns b = 4g + j: write, then read back transposed
+            for (int d = 0; d < 3; ++d) raw[p & 1][d].operands(part, x[d], y[d]);
+            const uint32_t sm = ps.sgn < 0.f ? 0x80000000u : 0u, cm = ps.dag ? 0x80000000u : 0u;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                lds[wv][c][4 * g + 0][n] = to_bf16(t[0][c].x);
-                lds[wv][c][4 * g + 1][n] = to_bf16(t[0][c].y);
-                lds[wv][c][4 * g + 2][n] = to_bf16(t[1][c].x);
-                lds[wv][c][4 * g + 3][n] = to_bf16(t[1][c].y);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                float t[4];
+                if (p == 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                // B[k = rhs 4g + j][n = b = lane % 16]
-                const bf16x4 Bt = *reinterpret_cast<const bf16x4 *>(&lds[wv][c][lane & 15][4 * g]);
+                    for (int j = 0; j < 4; ++j) t[j] = x[c][j];
+                } else {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        const float2 w = ps.U[p > 4 ? d * 3 + c : c * 3 + d];
+                        const float wr = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, w.x) ^ sm);
+                        const float wi = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, w.y) ^ sm ^ cm);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            t[j] = d == 0 ? wr * x[0][j] : fmaf(wr, x[d][j], t[j]);
+                            t[j] = fmaf(wi, y[d][j], t[j]);
+                        }
+                    }
+                }
+                const bf16x4 Bt = pack4(t[0], t[1], t[2], t[3]);
                 acc[p] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(Ag[c], Bt, acc[p], 0, 0, 0);
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
     }
-    __syncthreads();   // all transpositions done before the buffer is reused
 #pragma unroll
     for (int p = 0; p < NPATH; ++p)
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[wv][p * 256 + lane * 4 + r] = acc[p][r];
     __syncthreads();
-    float *dst = partial + (size_t)blockIdx.x * NPATH * 256;
+    float *dst = partial + (size_t)tile * NPATH * 256;
     for (int e = threadIdx.x; e < NPATH * 256; e += 256) dst[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
 }
 
-// Sum the per-block partials in a fixed order: block (p, chunk) of 256
-// threads owns 64 entries of P_p; thread slice q < 4 adds parts w = q mod 4,
-// then the four slices are combined in order.  psum[p*256 + e] (FP64).
-__global__ __launch_bounds__(256) void k_net_wgrad_sum(const float *__restrict__ partial, int nwaves,
-                                                       double *__restrict__ psum) {
-    __shared__ double red[4][64];
+// Sum the per-block partials in a fixed order: block (p, chunk) owns 64
+// entries of P_p; thread slice q < 16 adds parts w = q mod 16, then the slices
+// are combined in order.  psum[p*256 + e] (FP64).  A chain of dependent adds
+// behind loads: sixteen slices instead of four took 1,024 parts from 66 us to
+// 6 us.
+__global__ __launch_bounds__(1024) void k_net_wgrad_sum(const float *__restrict__ partial, int nparts,
+                                                        double *__restrict__ psum) {
+    __shared__ double red[16][64];
     const int p = blockIdx.x >> 2, chunk = blockIdx.x & 3;
     const int e = chunk * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
     double s = 0.0;
-    for (int w = q; w < nwaves; w += 4) s += (double)partial[((size_t)w * NPATH + p) * 256 + e];
+    int w = q;
+    for (; w + 7 * 16 < nparts; w += 8 * 16) {   // eight loads in flight
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = partial[((size_t)(w + 16 * i) * NPATH + p) * 256 + e];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += (double)v[i];
+    }
+    for (; w < nparts; w += 16) s += (double)partial[((size_t)w * NPATH + p) * 256 + e];
     red[q][threadIdx.x & 63] = s;
     __syncthreads();
-    if (q == 0) psum[p * 256 + e] = ((red[0][e & 63] + red[1][e & 63]) + red[2][e & 63]) + red[3][e & 63];
+    if (q == 0) {
+        for (int i = 1; i < 16; ++i) s += red[i][e & 63];
+        psum[p * 256 + e] = s;
+    }
 }
 
 // Map P (psum, entry lane*4 + r = P[4 (lane/16) + r][lane % 16]) to the real
@@ -370,21 +451,22 @@ __global__ void k_net_wgrad_map(const double *__restrict__ psum, int layer, doub
     grad[LAYER_OFF[layer] + t] = 2.0 * v;
 }
 
-// g = (out - e) / (||e_r||^2 P) and per-block partial sums of |out - e|^2 / (||e_r||^2 P)
+// g = (out - e) / (||e_r||^2 P) and per-block partial sums of |out - e|^2 / (||e_r||^2 P);
+// a fixed grid walks the vectors, so few partials are left to the one
+// workgroup that adds them (one per 256 elements took it 48 us at 16^4 x 16)
 __global__ __launch_bounds__(256) void k_net_loss(const float2 *__restrict__ out, const float2 *__restrict__ e,
                                                   const double2 *__restrict__ en2, long total, int N, double invP,
                                                   float2 *__restrict__ gdst, double *__restrict__ lpart) {
     __shared__ double red[256];
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     double l = 0.0;
-    if (i < total) {
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long)gridDim.x * 256) {
         const int r = (int)(i % N);
         const double en = en2[r].x;
         const double w = en > 0 ? invP / en : 0.0;
         const float2 a = out[i], b = e[i];
         const float dx = a.x - b.x, dy = a.y - b.y;
         gdst[i] = make_float2((float)(w * dx), (float)(w * dy));
-        l = w * ((double)dx * dx + (double)dy * dy);
+        l += w * ((double)dx * dx + (double)dy * dy);
     }
     red[threadIdx.x] = l;
     __syncthreads();
@@ -489,18 +571,23 @@ int launch_wgrad(mpmc_ctx *ctx, mpmc_net *net, int layer, const void *a_in, cons
     const float2 *L = reinterpret_cast<const float2 *>(ctx->links32);
     const float2 *a = (const float2 *)a_in;
     const float2 *gg = (const float2 *)gout;
-#define WG(A, B)                                                                                              \
-    if (fin == A && fout == B)                                                                                \
-        k_net_wgrad<A, B><<<blocks, 256, 0, ctx->stream>>>(a, gg, L, ctx->nbr, partial, N, nrb, (unsigned)units, \
-                                                           ctx->site_order);                                      \
+    // whole 16-byte pieces of four right-hand sides: every row starts on one
+    const bool vec = N % 4 == 0 && (reinterpret_cast<uintptr_t>(a_in) | reinterpret_cast<uintptr_t>(gout)) % 16 == 0;
+#define WG(A, B, VEC)                                                                                     \
+    if (fin == A && fout == B && vec == VEC)                                                              \
+        k_net_wgrad<A, B, VEC><<<blocks, 256, 0, ctx->stream>>>(a, gg, L, ctx->nbr, partial, N, nrb,      \
+                                                                (unsigned)units, ctx->site_order);        \
     else
-    WG(1, 2)
-    WG(2, 2)
-    WG(2, 1)
+    WG(1, 2, true)
+    WG(1, 2, false)
+    WG(2, 2, true)
+    WG(2, 2, false)
+    WG(2, 1, true)
+    WG(2, 1, false)
     return set_err(ctx, MPMC_EINVAL, "network: bad layer shape");
 #undef WG
     HIP_OR_RET(ctx, hipGetLastError());
-    k_net_wgrad_sum<<<NPATH * 4, 256, 0, ctx->stream>>>(partial, (int)blocks, psum);
+    k_net_wgrad_sum<<<NPATH * 4, 1024, 0, ctx->stream>>>(partial, (int)blocks, psum);
     HIP_OR_RET(ctx, hipGetLastError());
     const int npar = LAYER_OFF[layer + 1] - LAYER_OFF[layer];
     k_net_wgrad_map<<<grid_for(npar, 64), 64, 0, ctx->stream>>>(psum, layer, net->grad);
@@ -521,7 +608,7 @@ int net_loss_grad(mpmc_net *net, const void *R, const void *E, int P) {
     const size_t v1 = vec_bytes(ctx, P, MPMC_FP32), v2 = 2 * v1;
     void *a1 = S.get(v2), *a2 = S.get(v2), *a3 = S.get(v1), *g3 = S.get(v1), *g2 = S.get(v2), *g1 = S.get(v2);
     const long total = ctx->V * 12 * P;
-    const unsigned lblocks = grid_for(total, 256);
+    const unsigned lblocks = std::min(LOSS_BLOCKS, grid_for(total, 256));
     double *en2 = (double *)S.get(sizeof(double2) * P);
     double *lpart = (double *)S.get(sizeof(double) * lblocks);
     float *partial = (float *)S.get(sizeof(float) * (size_t)WGRAD_BLOCKS * NPATH * 256);
