@@ -939,6 +939,12 @@ int blas_multi_dot_h(mpmc_ctx *ctx, const void *Vb, size_t vstride_b, int nv, co
     return MPMC_OK;
 }
 
+int blas_reduce(mpmc_ctx *ctx, const void *part, int NB, int nj, int nrhs, double *out_dev) {
+    k_reduce<<<nj * nrhs, 256, 0, ctx->stream>>>((const double2 *)part, NB, nrhs, (double2 *)out_dev, 0, 0);
+    HIP_OR_RET(ctx, hipGetLastError());
+    return MPMC_OK;
+}
+
 int blas_dot(mpmc_ctx *ctx, const void *x, const void *y, int nrhs, int prec, int theta, double *out_dev) {
     return blas_multi_dot(ctx, x, 0, nrhs, 1, y, nrhs, prec, out_dev, 0, theta);
 }

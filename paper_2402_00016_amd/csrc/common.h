@@ -318,6 +318,8 @@ int launch_noise(mpmc_ctx *ctx, uint64_t seed, uint32_t stream, uint64_t first, 
 // shared by all right-hand sides, e.g. deflation vectors).
 int blas_multi_dot(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv, const void *w, int nrhs,
                    int prec, double *h_dev, int accumulate, int theta);
+// out[j*nrhs + r] = sum_b part[(j*NB + b)*nrhs + r], j < nj (fixed order)
+int blas_reduce(mpmc_ctx *ctx, const void *part, int NB, int nj, int nrhs, double *out_dev);
 int blas_dot(mpmc_ctx *ctx, const void *x, const void *y, int nrhs, int prec, int theta, double *out_dev);
 int blas_norm2(mpmc_ctx *ctx, const void *x, int nrhs, int prec, double *out_dev);
 int blas_multi_axpy(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv, void *w, int nrhs, int prec,
@@ -392,6 +394,9 @@ int poly_validate(const mpmc_ctx *ctx, const mpmc_poly *p);
 // Device address of `device`'s copy of the fixed scratch array of
 // mpmc_apply_poly_noalloc (looked up once per device); nullptr on failure.
 void *noalloc_scratch(int device);
+// acc[r] += sign * c * eta^H Theta eta for any Z(4) vector eta: 12 V or, with
+// Theta = gamma5, 0
+int quad_add_first(mpmc_ctx *ctx, int nrhs, int theta, double2 c, double sign, double *acc);
 // acc[r] += sign * eta_r^H Theta p(M) eta_r without forming p(M) eta (fused steps)
 int poly_quad_fused(mpmc_ctx *ctx, const mpmc_poly *p, const void *eta, const uint32_t *codes, int nrhs, int prec,
                     int theta, double *acc, double sign);

@@ -60,11 +60,88 @@ int defl_setup(mpmc_ctx *ctx, const mpmc_poly *upper, const mpmc_poly *lower, co
     return MPMC_OK;
 }
 
-// acc[r] -= sum_i c_i (eta_r^H Theta z_i)(u_i^H eta_r) for the noise vectors
-// first .. first+nb-1 of (seed, stream), regenerated in FP64 into eta64.
+// partial[j][blk][r], j < 2k: sums over the block's sites of conj(z_j) Theta eta_r
+// (j < k) and conj(u_{j-k}) eta_r (j >= k) with eta from its 2-bit codes (rows of
+// ld entries from column off), 64 right-hand sides a wavefront, one site at a
+// time: the eigenvectors are the same for all lanes and come through the
+// scalar cache, eta_k = i^sym is two factors 0 or +-1 per lane, so a component
+// costs four FP64 FMAs with exact products.  KG pairs a workgroup, codes read
+// again for each.  Bound by the FMAs and the scalar loads; 24^4 x 64, four pairs: 680 us, against
+// 2.56 ms for writing eta in FP64 and reading it for two dot products.
+constexpr int KG = 4;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_defl_codes(
+    const double2 *__restrict__ Z, const double2 *__restrict__ U, long n, int k, const uint32_t *__restrict__ codes,
+    int ld, int off, int N, long V, int theta, double2 *__restrict__ partial, int NB) {
+    __shared__ double2 red[2 * KG][256];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = blockIdx.y * 64 + lane, i0 = blockIdx.z * KG;
+    cpx<double> acc[2 * KG];
+#pragma unroll
+    for (int j = 0; j < 2 * KG; ++j) acc[j] = mk(0.0, 0.0);
+    const double tsg = theta ? -1.0 : 1.0;
+    for (long s = (long)blockIdx.x * 4 + wv; s < V; s += (long)NB * 4) {
+        const uint32_t code = codes[s * ld + off + r];
+        double er[12], ei[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const uint32_t sym = code >> (2 * c);
+            const double sg = (sym & 2u) ? -1.0 : 1.0;
+            er[c] = (sym & 1u) ? 0.0 : sg;
+            ei[c] = (sym & 1u) ? sg : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < KG; ++q) {
+            if (i0 + q >= k) break;
+            const double2 *z = Z + (i0 + q) * n + s * 12, *u = U + (i0 + q) * n + s * 12;
+            cpx<double> a = acc[q], b = acc[KG + q];
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                const double zx = c >= 6 ? tsg * z[c].x : z[c].x, zy = c >= 6 ? tsg * z[c].y : z[c].y;
+                a.re = fma(zx, er[c], fma(zy, ei[c], a.re));
+                a.im = fma(zx, ei[c], fma(-zy, er[c], a.im));
+                b.re = fma(u[c].x, er[c], fma(u[c].y, ei[c], b.re));
+                b.im = fma(u[c].x, ei[c], fma(-u[c].y, er[c], b.im));
+            }
+            acc[q] = a;
+            acc[KG + q] = b;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * KG; ++j) red[j][threadIdx.x] = make_double2(acc[j].re, acc[j].im);
+    __syncthreads();
+    for (int e = threadIdx.x; e < 2 * KG * 64; e += 256) {
+        const int j = e >> 6, l = e & 63, i = i0 + (j & (KG - 1));
+        if (i >= k) continue;
+        const double2 x0 = red[j][l], x1 = red[j][64 + l], x2 = red[j][128 + l], x3 = red[j][192 + l];
+        const int row = j < KG ? i : k + i;
+        partial[((long)row * NB + blockIdx.x) * N + blockIdx.y * 64 + l] =
+            make_double2(((x0.x + x1.x) + x2.x) + x3.x, ((x0.y + x1.y) + x2.y) + x3.y);
+    }
+}
+
+// acc[r] -= sum_i c_i (eta_r^H Theta z_i)(u_i^H eta_r) from the noise codes, nb a
+// multiple of 64; dab: 2 k nb entries of scratch.
+int defl_samples_codes(mpmc_ctx *ctx, const mpmc_defl *defl, const double2 *dcf, const uint32_t *codes, int ld, int off,
+                       int nb, int th, double2 *dab, double2 *acc) {
+    const int k = defl->k, groups = (k + KG - 1) / KG, chunks = nb / 64;
+    const int NB = (int)std::max<long>(1, std::min<long>((ctx->V + 3) / 4, (long)ctx->num_cu * 4 / std::min(chunks * groups, 16)));
+    double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, sizeof(double2) * 2 * (size_t)k * NB * nb);
+    if (!part) return MPMC_ENOMEM;
+    k_defl_codes<<<dim3(NB, chunks, groups), 256, 0, ctx->stream>>>((const double2 *)defl->Z, (const double2 *)defl->U,
+                                                                    ctx->n, k, codes, ld, off, nb, ctx->V, th, part, NB);
+    HIP_OR_RET(ctx, hipGetLastError());
+    RET_IF(blas_reduce(ctx, part, NB, 2 * k, nb, (double *)dab));
+    k_defl_term<<<grid_for(nb, 64), 64, 0, ctx->stream>>>(acc, dab, dab + (size_t)k * nb, dcf, k, nb);
+    HIP_OR_RET(ctx, hipGetLastError());
+    return MPMC_OK;
+}
+
+// The same for any nb: the noise vectors first .. first+nb-1 of (seed, stream)
+// regenerated in FP64 into eta64.
 int defl_samples(mpmc_ctx *ctx, const mpmc_defl *defl, const double2 *dcf, uint64_t seed, uint32_t stream,
-                 uint64_t first, int nb, int th, void *eta64, double2 *da, double2 *db, double2 *acc) {
+                 uint64_t first, int nb, int th, void *eta64, double2 *dab, double2 *acc) {
     const int k = defl->k;
+    double2 *da = dab, *db = dab + (size_t)k * nb;
     RET_IF(launch_noise(ctx, seed, stream, first, nb, MPMC_FP64, eta64));
     RET_IF(blas_multi_dot(ctx, defl->Z, ctx->n, 1, k, eta64, nb, MPMC_FP64, (double *)da, 0, th));
     RET_IF(blas_multi_dot(ctx, defl->U, ctx->n, 1, k, eta64, nb, MPMC_FP64, (double *)db, 0, 0));
@@ -107,13 +184,14 @@ MPMC_API int mpmc_level_estimate(mpmc_ctx *ctx, const mpmc_poly *upper, const mp
     const size_t vbp = vec_bytes(ctx, B, prec), vb64 = vec_bytes(ctx, B, MPMC_FP64);
     void *eta = S.get(std::max(vbp, vb64));
     void *yv = S.get(std::max(vbp, vb64));
-    void *eta64 = (!upper || use_defl) ? S.get(vb64) : nullptr;
+    // batches of whole 64-wide chunks take their deflation terms from the codes
+    const bool defl64 = use_defl && (B % 64 != 0 || (nnoise % B) % 64 != 0);
+    void *eta64 = (!upper || defl64) ? S.get(vb64) : nullptr;
     double2 *acc = (double2 *)S.get(sizeof(double2) * B);
     double2 *tmp = (double2 *)S.get(sizeof(double2) * B);
-    double2 *da = k ? (double2 *)S.get(sizeof(double2) * (size_t)k * B) : nullptr;
-    double2 *db = k ? (double2 *)S.get(sizeof(double2) * (size_t)k * B) : nullptr;
+    double2 *dab = k ? (double2 *)S.get(sizeof(double2) * 2 * (size_t)k * B) : nullptr;
     double2 *dcf = k ? (double2 *)S.get(sizeof(double2) * k) : nullptr;
-    if (!eta || !yv || !acc || !tmp || ((!upper || use_defl) && !eta64) || (k && (!da || !db || !dcf)))
+    if (!eta || !yv || !acc || !tmp || ((!upper || defl64) && !eta64) || (k && (!dab || !dcf)))
         return MPMC_ENOMEM;
 
     std::complex<double> corr(0, 0);
@@ -131,7 +209,8 @@ MPMC_API int mpmc_level_estimate(mpmc_ctx *ctx, const mpmc_poly *upper, const mp
         HIP_OR_RET(ctx, hipMemsetAsync(acc, 0, sizeof(double2) * nb, ctx->stream));
         if (upper || lower) {
             RET_IF(launch_noise(ctx, seed, stream, first + b0, nb, prec, eta));
-            if (fused) RET_IF(wilson_noise_codes(ctx, seed, stream, first + b0, nb, codes));
+            if (fused || (use_defl && nb % 64 == 0))
+                RET_IF(wilson_noise_codes(ctx, seed, stream, first + b0, nb, codes));
         }
         if (!upper) {
             int its = 0;
@@ -154,7 +233,10 @@ MPMC_API int mpmc_level_estimate(mpmc_ctx *ctx, const mpmc_poly *upper, const mp
                 RET_IF(blas_scale_acc(ctx, (double *)tmp, nb, make_double2(1, 0), signs[q], (double *)acc));
             }
         }
-        if (use_defl) RET_IF(defl_samples(ctx, defl, dcf, seed, stream, first + b0, nb, th, eta64, da, db, acc));
+        if (use_defl && nb % 64 == 0)
+            RET_IF(defl_samples_codes(ctx, defl, dcf, codes, nb, 0, nb, th, dab, acc));
+        else if (use_defl)
+            RET_IF(defl_samples(ctx, defl, dcf, seed, stream, first + b0, nb, th, eta64, dab, acc));
         HIP_OR_RET(ctx, hipMemcpyAsync(samples_host + 2 * (size_t)b0, acc, sizeof(double2) * nb, hipMemcpyDeviceToHost,
                                        ctx->stream));
     }
@@ -235,20 +317,17 @@ MPMC_API int mpmc_level_estimate_multi(mpmc_ctx *ctx, int nterms, const mpmc_pol
     void *wa = S.get(vb);
     void *wb = S.get(vb);
     uint32_t *codes = (uint32_t *)S.get(sizeof(uint32_t) * (size_t)ctx->V * N);
-    double2 *first_dot = (double2 *)S.get(sizeof(double2) * N);
     double2 *fin = (double2 *)S.get(sizeof(double2) * N);
     double2 *acc = (double2 *)S.get(sizeof(double2) * (size_t)nterms * nb);
     double *part = (double *)S.get(sizeof(double2) * wilson_dot_partial_count(ctx, N));
     const size_t steps = dmax >= 2 ? (size_t)dmax - 1 : 0;
     double2 *coef = steps ? (double2 *)S.get(sizeof(double2) * 2 * nch * steps) : nullptr;
     const int k = defl ? defl->k : 0;
-    void *eta64 = k ? S.get(vec_bytes(ctx, nb, MPMC_FP64)) : nullptr;
-    double2 *da = k ? (double2 *)S.get(sizeof(double2) * (size_t)k * nb) : nullptr;
-    double2 *db = k ? (double2 *)S.get(sizeof(double2) * (size_t)k * nb) : nullptr;
+    double2 *dab = k ? (double2 *)S.get(sizeof(double2) * 2 * (size_t)k * nb) : nullptr;
     double2 *dcf = k ? (double2 *)S.get(sizeof(double2) * k) : nullptr;
     double2 *uz = k ? (double2 *)S.get(sizeof(double2) * k) : nullptr;
-    if (!eta || !wa || !wb || !codes || !first_dot || !fin || !acc || !part || (steps && !coef) ||
-        (k && (!eta64 || !da || !db || !dcf || !uz)))
+    if (!eta || !wa || !wb || !codes || !fin || !acc || !part || (steps && !coef) ||
+        (k && (!dab || !dcf || !uz)))
         return MPMC_ENOMEM;
 
     auto inv = [&](const mpmc_poly *p, int i) {
@@ -261,7 +340,6 @@ MPMC_API int mpmc_level_estimate_multi(mpmc_ctx *ctx, int nterms, const mpmc_pol
         RET_IF(launch_noise(ctx, seed, st, first, nb, prec, eta, N, j * nb));
         RET_IF(wilson_noise_codes(ctx, seed, st, first, nb, codes, N, j * nb));
     }
-    RET_IF(blas_dot(ctx, eta, eta, N, prec, th, (double *)first_dot));   // eta^H Theta eta per right-hand side
     if (steps) {
         // coefficient table: step s, chunk q -> (1/theta_s, 1/theta_{s+1}) of the chunk's run
         std::vector<double2> tab(2 * nch * steps, make_double2(0, 0));
@@ -298,8 +376,7 @@ MPMC_API int mpmc_level_estimate_multi(mpmc_ctx *ctx, int nterms, const mpmc_pol
             const Rec &rc = recs[j];   // recs are in term order, upper before lower
             if (rc.term != t) continue;
             const int run = run_of[j];
-            RET_IF(blas_scale_acc(ctx, (const double *)(first_dot + (size_t)run * nb), nb, inv(rc.p, 0), rc.sign,
-                                  (double *)at));
+            RET_IF(quad_add_first(ctx, nb, th, inv(rc.p, 0), rc.sign, (double *)at));
             if (rc.p->d >= 2)
                 RET_IF(blas_scale_acc(ctx, (const double *)(fin + (size_t)run * nb), nb, make_double2(1, 0), rc.sign,
                                       (double *)at));
@@ -307,7 +384,9 @@ MPMC_API int mpmc_level_estimate_multi(mpmc_ctx *ctx, int nterms, const mpmc_pol
         std::complex<double> corr(0, 0);
         if (lower[t] && k > 0) {
             RET_IF(defl_setup(ctx, upper[t], lower[t], defl, th, dcf, uz, corr));
-            RET_IF(defl_samples(ctx, defl, dcf, seed, streams[t], first, nb, th, eta64, da, db, at));
+            int j0 = 0;   // a run of the term: upper and lower carry the same noise
+            while (recs[j0].term != t) ++j0;
+            RET_IF(defl_samples_codes(ctx, defl, dcf, codes, N, run_of[j0] * nb, nb, th, dab, at));
         }
         HIP_OR_RET(ctx, hipMemcpyAsync(samples_host + 2 * (size_t)t * nb, at, sizeof(double2) * nb,
                                        hipMemcpyDeviceToHost, ctx->stream));
