@@ -377,15 +377,19 @@ int mpmc_solve_batch(mpmc_ctx *const *ctxs, int count, const void *const *b, voi
  *   11       -- column streaming with 2 x 2 x 1 tiles (FP32, even Lx, Ly,
  *               Lt >= 4; else 5): 4 wavefronts per workgroup and half the
  *               LDS, so two workgroups share a compute unit; both z
- *               neighbours come from memory (5 reads per site);
+ *               neighbours come from memory (5 reads per site); in FP64
+ *               the only column kernel, one workgroup per compute unit, for
+ *               batches that fill the chip with them (Lx Ly Lz nrhs / 256
+ *               workgroups in rounds of one per compute unit at least about
+ *               3/4 full), else 4;
  *   12       -- column streaming with 2 x 2 x 4 tiles and 32-wide
  *               right-hand-side chunks (FP32, even Lx, Ly, Lz % 4 == 0,
  *               Lt >= 4, buffer ranges below 2 GiB; else 5): a wavefront holds
  *               two sites of a column pair (32 lanes each), so an XCD's
  *               concurrent workgroups cover twice the sites and fewer
  *               neighbours fall outside them (3.5 reads per site).
- * Defaults: variant 10 where it applies (FP32), else 5 for FP32/FP16S and 4
- * for FP64.
+ * Defaults: variant 10 (FP32) or 11 (FP64) where it applies, else 5 for
+ * FP32/FP16S and 4 for FP64.
  * mpmc_autotune times every variant on (nrhs, prec) with scratch vectors of
  * the context (2 warm-up + 5 timed launches each, HIP events) and keeps the
  * fastest for all later Wilson launches on ctx with that (nrhs, prec),
@@ -411,12 +415,12 @@ int mpmc_tune_set(mpmc_ctx *ctx, int nrhs, int prec, int variant);
 /* Autotune the fused polynomial step of mpmc_level_estimate (the dominant
  * kernel of the polynomial levels, Sec. 6): every traversal valid for the
  * shape -- order 0 site-major, 2 blocked 64-wide chunks, 3 / 4 blocked 16- /
- * 32-wide chunks (V % 16 == 0), 5 / 6 / 7 column streaming (FP32, as
- * variants 10 / 11 / 12) --
+ * 32-wide chunks (V % 16 == 0), 5 / 6 / 7 column streaming (as variants
+ * 10 / 11 / 12; FP64 as 11 only) --
  * is timed on (nrhs, prec) (2 warm-up + 5 timed steps, HIP events, best of
  * three interleaved rounds) and the fastest is kept for later level
  * estimates on ctx.  Without this call the step takes the column streaming
- * kernel with 2x2x2 tiles where it applies, else blocked 64-wide chunks
+ * kernel (2x2x2 tiles in FP32, 2x2x1 in FP64) where it applies, else blocked 64-wide chunks
  * (V % 4 == 0), else site-major.  prec FP64 or FP32, nrhs a multiple of 64
  * (and of 256 above 256).  order_host (may be NULL): the choice; us_host
  * (may be NULL): double[8] microseconds per step by order (0

@@ -212,6 +212,12 @@ struct SiteAcc {
     // FP32 store with the non-temporal policy (cache-policy bit 1): the L2
     // keeps the line first in line for eviction, leaving its capacity to lines
     // that other workgroups of the XCD are about to read
+    __device__ __forceinline__ void st_stream(int k, cpx<double> v) const {   // two halves: see stbuf
+        static_assert(kBuf && P == MPMC_FP64, "FP64 buffer accessor only");
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v.re), rs, (int)(r * 16u), k * N * 16, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v.im), rs, (int)(r * 16u + 8u), k * N * 16, 2);
+    }
     __device__ __forceinline__ void st_stream(int k, cpx<float> v) const {
         static_assert(kBuf && P == MPMC_FP32, "FP32 buffer accessor only");
         f32x2 d;
@@ -580,7 +586,7 @@ struct Occ {
 // links).  Orders 3 and 4 need V % 16 == 0; elsewhere they fall back to 2.
 constexpr int WILSON_VARIANTS = 13;
 constexpr int WILSON_COLUMN = 10;    // FP32 column-streaming kernel (k_wilson_col), 2x2x2 tiles
-constexpr int WILSON_COLUMN1 = 11;   // the same with 2x2x1 tiles (two workgroups per compute unit)
+constexpr int WILSON_COLUMN1 = 11;   // the same with 2x2x1 tiles (two workgroups per compute unit; FP64: k_wilson_col64)
 constexpr int WILSON_COLUMNP = 12;   // 2x2x4 tiles, 32-wide chunks, two sites per wavefront (k_wilson_colp)
 
 // Everything one thread does for (site s, rhs r) once located.
@@ -1924,6 +1930,254 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
+// ------------------------------------------------ column streaming, FP64 --
+// The walk of k_wilson_col with 2x2x1 tiles in FP64: a slice of four sites x 64
+// right-hand sides is 48 KB of LDS, three of them fill a compute unit, so it
+// runs four wavefronts with the whole register file between them.  Latency is
+// hidden inside a wavefront instead: the four out-of-tile neighbours, the t+1
+// site and the links of the next step are all in flight while a step computes.
+// Five spinor reads per site instead of nine; an XCD's round of 32 workgroups
+// is a block of 8x4x4 sites (8x8x4 ones, two rounds each, leave the second
+// round's neighbours to memory: 546 us).  Bound by L2-miss traffic and, with
+// one wavefront per SIMD, by the chain of loads and FP64 FMAs in a step; 16^4 x
+// 64: 482 us against 631 us blocked (3,420 GB/s of algorithmic bytes), fused
+// step 505 against 701 us; 24^4 x 64: 2.58 against 3.18 ms.  Same arithmetic as the blocked
+// kernels (apply, then wilson_site's or k_wilson_dot's epilogue), same bits.
+struct Col64Lds {
+    double2 v[3][4][12][64];
+};
+typedef cpx<double> Spin64[12];
+__device__ __forceinline__ void col64_load(const void *b, long site, int N, uint32_t r, Spin64 &psi) {
+    const SiteAcc<MPMC_FP64, true> A(b, nullptr, site, N, r);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) psi[k] = A.ld(k);
+}
+__device__ __forceinline__ void col64_read(const Col64Lds &L, int buf, int w, unsigned lane, Spin64 &psi) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const double2 v = L.v[buf][w][k][lane];
+        psi[k] = mk(v.x, v.y);
+    }
+}
+__device__ __forceinline__ void col64_publish(Col64Lds &L, int buf, int w, unsigned lane, const Spin64 &psi) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) L.v[buf][w][k][lane] = make_double2(psi[k].re, psi[k].im);
+}
+template <int MU, bool FWD>
+__device__ __forceinline__ void col64_hop(const Spin64 &psi, uint32_t lw, double bsign, float g, cpx<double> acc[4][3]) {
+    HopData<MPMC_FP64> H;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) H.psi[k] = psi[k];
+    H.lw[0] = lw;
+    H.bsign = bsign;
+    apply<MPMC_FP64, true, MU, FWD>(H, g, acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+// x or y: the partner from LDS, the out-of-tile neighbour from registers
+template <int MU>
+__device__ __forceinline__ void col64_dir(const Col64Lds &L, int buf, int w, unsigned lane, int upper, const Spin64 &og,
+                                          uint32_t lf, uint32_t lb, float g, cpx<double> acc[4][3]) {
+    Spin64 nb;
+    col64_read(L, buf, w ^ (1 << MU), lane, nb);
+    if (!upper) {
+        col64_hop<MU, true>(nb, lf, 1.0, g, acc);
+        col64_hop<MU, false>(og, lb, 1.0, g, acc);
+    } else {
+        col64_hop<MU, true>(og, lf, 1.0, g, acc);
+        col64_hop<MU, false>(nb, lb, 1.0, g, acc);
+    }
+}
+
+template <int MODE, bool CMB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_wilson_col64(
+    const void *__restrict__ b, const double2 *__restrict__ links, ColArgs ca, int N, WOut o,
+    const uint32_t *__restrict__ codes, double2 c, double2 cnext, int theta, double2 *__restrict__ partial,
+    int first_step, const void *__restrict__ a2, double2 alpha, double2 beta) {
+    using T = double;
+    __shared__ Col64Lds L;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned lane = threadIdx.x & 63u;
+    const int wx = w & 1, wy = w >> 1;
+    // XCD rounds and the z-first snake of blocks exactly as in k_wilson_col
+    const int bsz = ca.bx * ca.by * ca.bz, nbx = ca.ntx / ca.bx, nbz = ca.ntz / ca.bz;
+    const long xcd = blockIdx.x % 8u, slot = blockIdx.x / 8u;
+    const long lbk = slot / bsz;
+    const long gb0 = lbk * 8 + xcd;
+    if (gb0 >= ca.nblk) return;
+    const long gb = ca.rev ? ca.nblk - 1 - gb0 : gb0;
+    const long nbc = ca.ntiles / bsz;
+    const long chunk = gb / nbc, blk = gb - chunk * nbc;
+    const int in = (int)(slot - lbk * bsz);
+    const unsigned tile = (unsigned)(chunk * ca.ntiles + blk * bsz + in);
+    const long zrow = blk / nbz;
+    const int bzi = (int)(zrow & 1 ? nbz - 1 - (blk - zrow * nbz) : blk - zrow * nbz);
+    const int xrow = (int)(zrow / nbx);
+    const int bxi = (int)(xrow & 1 ? nbx - 1 - (zrow - (long)xrow * nbx) : zrow - (long)xrow * nbx);
+    const int x = 2 * (bxi * ca.bx + in % ca.bx) + wx, y = 2 * (xrow * ca.by + (in / ca.bx) % ca.by) + wy;
+    const int z = bzi * ca.bz + in / (ca.bx * ca.by), Lt = ca.L[3];
+    const uint32_t r = (uint32_t)(chunk * 64 + lane);
+    const int xf = x + 1 == ca.L[0] ? 0 : x + 1, xb = x == 0 ? ca.L[0] - 1 : x - 1;
+    const int yf = y + 1 == ca.L[1] ? 0 : y + 1, yb = y == 0 ? ca.L[1] - 1 : y - 1;
+    const int zf = z + 1 == ca.L[2] ? 0 : z + 1, zb = z == 0 ? ca.L[2] - 1 : z - 1;
+    const int xo = wx ? xf : xb, yo = wy ? yf : yb;
+    const float g = o.g;
+    const T kap = o.kappa;
+
+    {
+        Spin64 v;
+        col64_load(b, col_site(ca, x, y, z, Lt - 1), N, r, v);
+        col64_publish(L, 2, w, lane, v);
+        col64_load(b, col_site(ca, x, y, z, 0), N, r, v);
+        col64_publish(L, 0, w, lane, v);
+    }
+    // links of step t: U_mu(s), then U_x, U_y, U_z of the backward sites; the
+    // next step's are fetched during this one
+    uint32_t lk[7], lkn[7], ltprev[1];
+    auto fetch_links = [&](int t, uint32_t (&q)[7]) {
+        const long s = col_site(ca, x, y, z, t);
+        uint32_t one[2];
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            load_link_lanes<MPMC_FP64>(links + (s * 4 + mu) * 9, one);
+            q[mu] = one[0];
+        }
+        load_link_lanes<MPMC_FP64>(links + (col_site(ca, xb, y, z, t) * 4 + 0) * 9, one);
+        q[4] = one[0];
+        load_link_lanes<MPMC_FP64>(links + (col_site(ca, x, yb, z, t) * 4 + 1) * 9, one);
+        q[5] = one[0];
+        load_link_lanes<MPMC_FP64>(links + (col_site(ca, x, y, zb, t) * 4 + 2) * 9, one);
+        q[6] = one[0];
+    };
+    {
+        uint32_t one[2];
+        load_link_lanes<MPMC_FP64>(links + (col_site(ca, x, y, z, Lt - 1) * 4 + 3) * 9, one);
+        ltprev[0] = one[0];
+    }
+    fetch_links(0, lk);
+    Spin64 ogx, ogy, ogf, ogb;
+    col64_load(b, col_site(ca, xo, y, z, 0), N, r, ogx);
+    col64_load(b, col_site(ca, x, yo, z, 0), N, r, ogy);
+    col64_load(b, col_site(ca, x, y, zf, 0), N, r, ogf);
+    col64_load(b, col_site(ca, x, y, zb, 0), N, r, ogb);
+    cpx<double> dot = mk(0.0, 0.0);
+
+    for (int t = 0; t < Lt; ++t) {
+        const int curb = t % 3, prevb = (t + 2) % 3, nextb = (t + 1) % 3;
+        const long s = col_site(ca, x, y, z, t);
+        const int tn = t + 1 < Lt ? t + 1 : 0;   // at the end: t = 0 again (the forward t neighbour)
+        Spin64 nx;
+        col64_load(b, col_site(ca, x, y, z, tn), N, r, nx);
+        const uint32_t code = MODE == 1 ? __builtin_nontemporal_load(codes + s * N + r) : 0u;
+        fetch_links(tn, lkn);
+        __syncthreads();   // slice t published by every wavefront, step t-1 read
+
+        cpx<T> acc[4][3];
+#pragma unroll
+        for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) acc[sp][cc] = mk(0.0, 0.0);
+        col64_dir<0>(L, curb, w, lane, wx, ogx, lk[0], lk[4], g, acc);
+        col64_load(b, col_site(ca, xo, y, z, tn), N, r, ogx);
+        __builtin_amdgcn_sched_barrier(0);
+        col64_dir<1>(L, curb, w, lane, wy, ogy, lk[1], lk[5], g, acc);
+        col64_load(b, col_site(ca, x, yo, z, tn), N, r, ogy);
+        __builtin_amdgcn_sched_barrier(0);
+        col64_hop<2, true>(ogf, lk[2], 1.0, g, acc);
+        col64_load(b, col_site(ca, x, y, zf, tn), N, r, ogf);
+        __builtin_amdgcn_sched_barrier(0);
+        col64_hop<2, false>(ogb, lk[6], 1.0, g, acc);
+        col64_load(b, col_site(ca, x, y, zb, tn), N, r, ogb);
+        __builtin_amdgcn_sched_barrier(0);
+        col64_hop<3, true>(nx, lk[3], (ca.tap && t == Lt - 1) ? -1.0 : 1.0, g, acc);
+        {
+            Spin64 pv;
+            col64_read(L, prevb, w, lane, pv);
+            col64_hop<3, false>(pv, ltprev[0], (ca.tap && t == 0) ? -1.0 : 1.0, g, acc);
+        }
+        pin_acc(acc);
+        col64_publish(L, nextb, w, lane, nx);
+
+        Spin64 cur;
+        col64_read(L, curb, w, lane, cur);
+        const SiteAcc<MPMC_FP64, true> O(o.out, nullptr, s, N, r);
+        if constexpr (MODE == 0) {
+            const bool has_a = o.a_is_b || o.a;
+            const cpx<T> al = has_a ? mk(o.alpha.x, o.alpha.y) : mk(0.0, 0.0);
+            const cpx<T> be = mk(o.beta.x, o.beta.y);
+            const cpx<T> beg5 = o.theta ? mk(-be.re, -be.im) : be;
+            Spin64 av;
+            if (o.a && !o.a_is_b) {
+                col64_load(o.a, s, N, r, av);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) av[k] = cur[k];
+            }
+            cpx<T> res[12];
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const cpx<T> mb = cur[k] - kap * acc[k / 3][k % 3];
+                res[k] = (k >= 6 ? beg5 : be) * mb + al * av[k];
+                O.st_stream(k, res[k]);
+            }
+            if (o.y) {
+                const cpx<T> ga = mk(o.gamma.x, o.gamma.y);
+                const SiteAcc<MPMC_FP64, true> Y(o.y, nullptr, s, N, r);
+                cpx<T> yv[12];
+#pragma unroll
+                for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+#pragma unroll
+                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + ga * res[k]);
+            }
+        } else {
+            const cpx<T> ccf = mk(c.x, c.y);
+            Spin64 av;
+            if constexpr (CMB) col64_load(a2, s, N, r, av);
+            const cpx<T> al = mk(alpha.x, alpha.y), be = mk(beta.x, beta.y);
+            const T tsg = theta ? T(-1) : T(1);
+            T sr = T(0), si = T(0);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const cpx<T> mw = cur[k] - kap * acc[k / 3][k % 3];
+                cpx<T> wn = cur[k] - ccf * mw;
+                if constexpr (CMB) wn = al * av[k] + be * wn;
+                O.st_stream(k, wn);
+                const uint32_t sym = (code >> (2 * k)) & 3u;
+                const T sg = (sym & 2u) ? T(-1) : T(1);
+                const T gg = k >= 6 ? sg * tsg : sg;
+                sr += gg * ((sym & 1u) ? wn.im : wn.re);
+                si += gg * ((sym & 1u) ? -wn.re : wn.im);
+            }
+            dot.re += sr;
+            dot.im += si;
+        }
+        ltprev[0] = lk[3];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) lk[q] = lkn[q];
+    }
+    if constexpr (MODE == 1) {
+        __syncthreads();   // every wavefront is done with the slices
+        double2 *red = &L.v[0][0][0][0];
+        red[threadIdx.x] = make_double2(dot.re, dot.im);
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            double sx = 0, sy = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sx += red[q * 64 + threadIdx.x].x;
+                sy += red[q * 64 + threadIdx.x].y;
+            }
+            const cpx<double> term = mk(cnext.x, cnext.y) * mk(sx, sy);
+            double2 *pp = partial + (long)tile * 64 + threadIdx.x;
+            if (first_step) {
+                *pp = make_double2(term.re, term.im);
+            } else {
+                const double2 old = *pp;
+                *pp = make_double2(old.x + term.re, old.y + term.im);
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------- launch --
 
 static double spinor_bytes(int prec) { return prec == MPMC_FP64 ? 192.0 : (prec == MPMC_FP32 ? 96.0 : 52.0); }
@@ -1940,7 +2194,7 @@ static bool col_ok(const mpmc_ctx *ctx, int nrhs, int prec, int tz = 2) {
     const double range = ((double)ctx->dims[0] * ctx->dims[1] + 1) * 12.0 * nrhs * 8.0;
     return range < 2147483648.0 && (double)ctx->V * 288.0 < 2147483648.0;
 }
-static ColArgs col_args(const mpmc_ctx *ctx, int tz = 2) {
+static ColArgs col_args(const mpmc_ctx *ctx, int tz = 2, bool fp64 = false) {
     ColArgs a;
     for (int mu = 0; mu < 4; ++mu) a.L[mu] = ctx->dims[mu];
     a.ntx = ctx->dims[0] / 2;
@@ -1954,7 +2208,7 @@ static ColArgs col_args(const mpmc_ctx *ctx, int tz = 2) {
         return want;
     };
     a.bx = ext(a.ntx, 4);
-    a.by = ext(a.nty, 4);
+    a.by = ext(a.nty, fp64 ? 2 : 4);      // FP64: one 2x2x1 tile per compute unit, 8x4x4 sites
     a.bz = ext(a.ntz, tz == 1 ? 4 : 2);   // 2x2x4 tiles: 4x4x2 of them, 8x8x8 sites
     a.ntiles = (long)a.ntx * a.nty * a.ntz;
     a.nblk = 0;
@@ -1968,8 +2222,25 @@ static unsigned col_grid(ColArgs &ca, int nrhs, int width = 64) {
     ca.nblk = ca.ntiles / bsz * (nrhs / width);
     return (unsigned)(8 * ((ca.nblk + 7) / 8) * bsz);
 }
+// FP64 column kernel (2x2x1 tiles): even Lx, Ly, Lt >= 4, 64-wide chunks, and
+// rounds of workgroups that fill the chip.  A round of one workgroup per
+// compute unit takes ~7.3 us per t step (and one step more to start), the
+// blocked kernel 9.6 us per 1,000 sites x 64 right-hand sides, so a round has
+// to hold 3/4 of a full one and its start: 16^4 x 64 (4 full rounds) 482
+// against 631 us, fused step 505 against 701; 12^4 x 64 (2 rounds, 84% full)
+// 176 against 213 us; 8^4 x 128 (one full round) 62 against 80 us; 8^4 x 64
+// (half a round) 55 against 42 us.  Blocks of fewer than 8 tiles leave too
+// many neighbours outside an XCD's L2 (10 x 14 x 7 x 22 x 64: 258 against 252 us).
+static bool col64_ok(const mpmc_ctx *ctx, int nrhs) {
+    if (nrhs % 64 != 0 || ctx->dims[0] % 2 != 0 || ctx->dims[1] % 2 != 0 || ctx->dims[3] < 4) return false;
+    ColArgs a = col_args(ctx, 1, true);
+    const long bsz = (long)a.bx * a.by * a.bz, wgs = a.ntiles * (nrhs / 64), Lt = ctx->dims[3];
+    const long per_xcd = (wgs / bsz + 7) / 8 * bsz, rounds = (per_xcd * 8 + ctx->num_cu - 1) / ctx->num_cu;
+    return bsz >= 8 && wgs * Lt * 4 >= rounds * (Lt + 1) * ctx->num_cu * 3;
+}
 static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
     if (col_ok(ctx, nrhs, prec)) return WILSON_COLUMN;
+    if (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) return WILSON_COLUMN1;
     return prec == MPMC_FP64 ? 4 : 5;
 }
 static double link_bytes(int prec) { return prec == MPMC_FP64 ? 576.0 : 288.0; }
@@ -1991,21 +2262,22 @@ static int wilson_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
     const auto it = ctx->tune.find(std::make_pair(nrhs, prec));
     const int v = it == ctx->tune.end() ? default_variant(ctx, nrhs, prec) : it->second;
     if (v == WILSON_COLUMN) return col_ok(ctx, nrhs, prec) ? v : (prec == MPMC_FP64 ? 4 : 5);
-    if (v == WILSON_COLUMN1) return col_ok(ctx, nrhs, prec, 1) ? v : (prec == MPMC_FP64 ? 4 : 5);
+    if (v == WILSON_COLUMN1)
+        return col_ok(ctx, nrhs, prec, 1) || (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) ? v : (prec == MPMC_FP64 ? 4 : 5);
     if (v == WILSON_COLUMNP) return col_ok(ctx, nrhs, prec, 4) ? v : (prec == MPMC_FP64 ? 4 : 5);
     return (v >> 1) >= 3 && ctx->V % 16 != 0 ? (v & 1) | 4 : v;
 }
 
-// The fused level step (FP32) takes the column kernel with 2x2x2 tiles where
-// the lattice allows it; otherwise (FP64 and other shapes) the 64-wide
+// The fused level step takes the column kernel (FP32: 2x2x2 tiles, FP64:
+// 2x2x1) where the shape allows it; otherwise the 64-wide
 // blocked order whenever its chunk tiles hold one chunk each (V % 4 == 0),
 // and the site-major order otherwise;
 // a variant set explicitly for (nrhs, prec) with mpmc_tune_set selects its
 // traversal (orders 0 and 1: site-major; 3 and 4 need V % 16 == 0), and
 // otherwise mpmc_autotune_level's choice, once made, replaces the default.
-constexpr int kDotDefaultOrder = 2;   // 64-wide blocked chunks (FP64; FP32 takes the column kernel)
+constexpr int kDotDefaultOrder = 2;   // 64-wide blocked chunks (where no column kernel applies)
 constexpr int kDotColumn = 5;         // order code of the column-streaming fused step (2x2x2 tiles)
-constexpr int kDotColumn1 = 6;        // the same with 2x2x1 tiles
+constexpr int kDotColumn1 = 6;        // the same with 2x2x1 tiles (and the FP64 one)
 constexpr int kDotColumnP = 7;        // 2x2x4 tiles, 32-wide chunks (k_wilson_colp)
 constexpr int kDotOrders = 8;
 static bool is_col_order(int o) { return o == kDotColumn || o == kDotColumn1 || o == kDotColumnP; }
@@ -2018,6 +2290,9 @@ static int dot_order(const mpmc_ctx *ctx, int nrhs, int prec) {
     }
     const auto it = ctx->tune_explicit.find(std::make_pair(nrhs, prec));
     if (it != ctx->tune_explicit.end() && it->second == WILSON_COLUMN1 && col_ok(ctx, nrhs, prec, 1) && nrhs <= 256)
+        return kDotColumn1;
+    if (prec == MPMC_FP64 && (it == ctx->tune_explicit.end() || it->second == WILSON_COLUMN1) && col64_ok(ctx, nrhs) &&
+        nrhs <= 256)
         return kDotColumn1;
     if (it != ctx->tune_explicit.end() && it->second == WILSON_COLUMNP && col_ok(ctx, nrhs, prec, 4) && nrhs <= 256)
         return kDotColumnP;
@@ -2113,6 +2388,15 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs, double2 yi
         if (cv == WILSON_COLUMN1) {
             ColArgs ca = col_args(ctx, 1);
             k_wilson_col<0, false, 1><<<col_grid(ca, nrhs), 256, 0, ctx->stream>>>(
+                in.b, in.links, ca, nrhs, o, nullptr, make_double2(0, 0), make_double2(0, 0), 0, nullptr, 0, nullptr,
+                make_double2(0, 0), make_double2(1, 0));
+            return;
+        }
+    }
+    if constexpr (P == MPMC_FP64) {
+        if (nrhs % 64 == 0 && wilson_variant(ctx, nrhs, P) == WILSON_COLUMN1) {
+            ColArgs ca = col_args(ctx, 1, true);
+            k_wilson_col64<0, false><<<col_grid(ca, nrhs), 256, 0, ctx->stream>>>(
                 in.b, in.links, ca, nrhs, o, nullptr, make_double2(0, 0), make_double2(0, 0), 0, nullptr, 0, nullptr,
                 make_double2(0, 0), make_double2(1, 0));
             return;
@@ -2244,6 +2528,19 @@ static void launch_dot(mpmc_ctx *ctx, int dord, unsigned grid, const WIn<P> &in,
             else
                 k_wilson_col<1, CMB, 1><<<grid_c, 256, 0, ctx->stream>>>(
                     in.b, in.links, ca, nrhs, o, codes, c, cnext, theta, partial, first_step, a, alpha, beta);
+            return;
+        }
+    }
+    if constexpr (P == MPMC_FP64) {
+        if (dord == kDotColumn1) {
+            ColArgs ca = col_args(ctx, 1, true);
+            ca.rev = (int)(ctx->col_flip++ & 1u);
+            WOut o{};
+            o.out = wout;
+            o.kappa = ctx->kappa;
+            o.g = 1.f;
+            k_wilson_col64<1, CMB><<<col_grid(ca, nrhs), 256, 0, ctx->stream>>>(
+                in.b, in.links, ca, nrhs, o, codes, c, cnext, theta, partial, first_step, a, alpha, beta);
             return;
         }
     }
@@ -2550,7 +2847,8 @@ MPMC_API int mpmc_autotune_level(mpmc_ctx *ctx, int nrhs, int prec, int *order_h
         cand.push_back(4);
     }
     if (col_ok(ctx, nrhs, prec) && nrhs <= 256) cand.push_back(kDotColumn);
-    if (col_ok(ctx, nrhs, prec, 1) && nrhs <= 256) cand.push_back(kDotColumn1);
+    if ((col_ok(ctx, nrhs, prec, 1) || (prec == MPMC_FP64 && col64_ok(ctx, nrhs))) && nrhs <= 256)
+        cand.push_back(kDotColumn1);
     if (col_ok(ctx, nrhs, prec, 4) && nrhs <= 256) cand.push_back(kDotColumnP);
     int best = cand.back(), rc = MPMC_OK;
     double best_us = 1e300;
