@@ -346,6 +346,10 @@ int blas_scale_rhs(mpmc_ctx *ctx, const void *x, void *y, int nrhs, int prec, co
 int blas_convert(mpmc_ctx *ctx, const void *x, int px, void *y, int py, int nrhs);
 // y (FP16S) = coef[r] x (FP32), coef per rhs (complex FP64, device)
 int blas_convert_scaled_h(mpmc_ctx *ctx, const void *x, void *y, int nrhs, const double *coef_dev);
+// x (FP64) += sum_j y[j*nrhs + r] V_j; y (prec) = x (FP64) / sqrt(re nrm[r])
+int blas_solution_add(mpmc_ctx *ctx, const void *Vb, size_t vstride_b, int nv, int prec, void *x, int nrhs,
+                      const double *y_dev);
+int blas_convert_normalised(mpmc_ctx *ctx, const void *x, void *y, int prec, int nrhs, const double *nrm_dev);
 int blas_zero(mpmc_ctx *ctx, void *y, int nrhs, int prec);
 int blas_scale_acc(mpmc_ctx *ctx, const double *t, int N, double2 c, double sign, double *acc);
 

@@ -136,7 +136,7 @@ int Gmres::init() {
     V_ = S_.get(vbb_ * (m + 1));
     Zb_ = net_ ? S_.get(vbi_ * m) : nullptr;   // flexible GMRES: preconditioned basis z_j = N v_j
     w_ = S_.get(vbi_);
-    corr_ = S_.get(vbi_);
+    corr_ = pp_ ? S_.get(vbi_) : nullptr;        // V y before p(M)
     tp_ = pp_ ? S_.get(vbi_) : nullptr;          // p(M) v_j (polynomial right preconditioning)
     tq_ = (pp_ || net_) && half_ ? S_.get(vbi_) : nullptr;  // FP32 copy of an FP16S basis vector
     H_ = (double *)S_.get(sizeof(double2) * (size_t)(m + 1) * (m + 1) * N);
@@ -149,7 +149,7 @@ int Gmres::init() {
     dc_ = defl_ && defl_->k ? (double *)S_.get(sizeof(double2) * (size_t)defl_->k * N) : nullptr;
     xsnap_ = snap_ ? S_.get(vb64_ * (size_t)snap_->max) : nullptr;   // FP64 iterates x_k of the record
     if (snap_ && !xsnap_) return MPMC_ENOMEM;
-    if (!r_ || !V_ || (net_ && !Zb_) || (pp_ && !tp_) || ((pp_ || net_) && half_ && !tq_) || !w_ || !corr_ || !H_ || !h2_ ||
+    if (!r_ || !V_ || (net_ && !Zb_) || (pp_ && !tp_) || ((pp_ || net_) && half_ && !tq_) || !w_ || (pp_ && !corr_) || !H_ || !h2_ ||
         !cs_ || !g_ || !y_ || !res_ || !sc_ || (defl_ && defl_->k && !dc_))
         return MPMC_ENOMEM;
     nrm_ = sc_;
@@ -236,14 +236,7 @@ int Gmres::begin_cycle(bool *go) {
         if (half_) t = std::max(t, 1e-3 * rn);   // FP16 basis: the Arnoldi relation holds to ~2^-11
         target_[i] = t;
     }
-    if (half_) {
-        RET_IF(blas_convert(ctx, r_, MPMC_FP64, w_, MPMC_FP32, N));
-        RET_IF(blas_scale_rhs(ctx, w_, w_, N, MPMC_FP32, nrm_, 1));
-        RET_IF(blas_convert(ctx, w_, MPMC_FP32, V_, MPMC_FP16S, N));
-    } else {
-        RET_IF(blas_convert(ctx, r_, MPMC_FP64, V_, inner_prec_, N));
-        RET_IF(blas_scale_rhs(ctx, V_, V_, N, inner_prec_, nrm_, 1));
-    }
+    RET_IF(blas_convert_normalised(ctx, r_, V_, pb_, N, nrm_));   // v_0 = r / ||r||
     HIP_OR_RET(ctx, hipMemsetAsync(H_, 0, sizeof(double2) * (size_t)(m + 1) * (m + 1) * N, ctx->stream));
     k_init_g<<<grid_for((long)(m + 1) * N, 256), 256, 0, ctx->stream>>>((double2 *)g_, m, N, (const double2 *)nrm_);
     HIP_OR_RET(ctx, hipGetLastError());
@@ -336,20 +329,20 @@ int Gmres::end_cycle() {
     mpmc_ctx *ctx = ctx_;
     const int N = N_, m = m_;
     RET_IF(dense_backsolve(ctx, H_, m + 1, jdone_, N, g_, y_));
-    HIP_OR_RET(ctx, hipMemsetAsync(corr_, 0, vbi_, ctx->stream));
-    if (cnet_)   // flexible GMRES: e = Z y (FP32)
-        RET_IF(blas_multi_axpy(ctx, Zb_, vstride_, N, jdone_, corr_, N, pw_, y_, N, 1.0, nullptr));
-    else if (half_)
-        RET_IF(blas_multi_axpy_h(ctx, V_, vbb_, jdone_, corr_, N, y_, N, 1.0, nullptr));
-    else
-        RET_IF(blas_multi_axpy(ctx, V_, vstride_, N, jdone_, corr_, N, inner_prec_, y_, N, 1.0, nullptr));
-    if (pp_) {   // correction p(M) V y
+    if (pp_) {   // x += p(M) V y
+        HIP_OR_RET(ctx, hipMemsetAsync(corr_, 0, vbi_, ctx->stream));
+        if (half_)
+            RET_IF(blas_multi_axpy_h(ctx, V_, vbb_, jdone_, corr_, N, y_, N, 1.0, nullptr));
+        else
+            RET_IF(blas_multi_axpy(ctx, V_, vstride_, N, jdone_, corr_, N, inner_prec_, y_, N, 1.0, nullptr));
         RET_IF(poly_apply_internal(ctx, pp_, corr_, tp_, N, pw_));
-        HIP_OR_RET(ctx, hipMemcpyAsync(corr_, tp_, vbi_, hipMemcpyDeviceToDevice, ctx->stream));
+        RET_IF(blas_convert(ctx, tp_, pw_, r_, MPMC_FP64, N));
+        RET_IF(blas_axpby(ctx, r_, x_, N, MPMC_FP64, make_double2(1, 0), make_double2(1, 0)));
+    } else if (cnet_) {   // flexible GMRES: x += Z y (FP32)
+        RET_IF(blas_solution_add(ctx, Zb_, vbi_, jdone_, MPMC_FP32, x_, N, y_));
+    } else {
+        RET_IF(blas_solution_add(ctx, V_, half_ ? vbb_ : (size_t)vstride_ * es_, jdone_, pb_, x_, N, y_));
     }
-    // x += e (in FP64)
-    RET_IF(blas_convert(ctx, corr_, pw_, r_, MPMC_FP64, N));
-    RET_IF(blas_axpby(ctx, r_, x_, N, MPMC_FP64, make_double2(1, 0), make_double2(1, 0)));
     total_ += jdone_;
     return MPMC_OK;
 }
