@@ -355,11 +355,13 @@ int blas_scale_acc(mpmc_ctx *ctx, const double *t, int N, double2 c, double sign
 
 // wilson.hip: out (FP32) = M b for an FP16S operand b
 int wilson_apply_h2f(mpmc_ctx *ctx, const void *b, void *out, int nrhs);
-// wilson.hip: out = alpha a + beta Theta op(b); y += gamma out (y may be null);
-// yinit_on (single vectors, a == b): y = yinit b + gamma out, y not read
+// wilson.hip: out = alpha a + beta Theta op(b) (out may be null if y is not);
+// y (may be null) takes gamma out, with kYAddB delta b before it, and with
+// kYInit y = delta b + gamma out, y not read
+constexpr int kYAdd = 0, kYAddB = 1, kYInit = 2;
 int wilson_launch_full(mpmc_ctx *ctx, const void *b, const void *a, void *out, void *y, int nrhs, int prec,
                        double2 alpha, double2 beta, double2 gamma, int dagger, int theta,
-                       double2 yinit = double2{0.0, 0.0}, int yinit_on = 0);
+                       double2 delta = double2{0.0, 0.0}, int ymode = kYAdd);
 // fused level step (see wilson.hip): w' = w - c M w; partial += cnext eta^H Theta w'
 size_t wilson_dot_partial_count(const mpmc_ctx *ctx, int nrhs);
 // codes of noise vectors first .. first+nrhs-1 into columns off .. of rows of

@@ -23,7 +23,7 @@
 // can be written out as FP32 (the FP16 Krylov bases of the solves).
 //
 // Kernels:
-//   k_wilson     out = alpha a + beta Theta op(b) [; y += gamma out]
+//   k_wilson     out = alpha a + beta Theta op(b) [; y += [delta b +] gamma out]
 //   k_wilson_dot one step of a polynomial recurrence on a batch of noise
 //                vectors, w' = w - c M w, without forming p(M) eta: the
 //                quadratic form eta^H Theta w' is accumulated on the fly
@@ -557,18 +557,41 @@ __device__ __forceinline__ bool locate(long V, int N, long &s, int &r, const int
 }
 
 struct WOut {
-    void *out;
+    void *out;              // nullptr (with y only): not stored
     float *osc;
     const void *a;          // additive term (nullptr: none; == b: reuse the operand)
     const float *asc;
-    void *y;                // y += gamma * out (nullptr: none)
+    void *y;                // sum of a polynomial (nullptr: none), see ymode
     double kappa;
-    double2 alpha, beta, gamma;
+    double2 alpha, beta, gamma, delta;
     float g;
     int theta;
     int a_is_b;
     int out_fp32;           // FP16S kernels only: write out as FP32 (plain out = M b)
+    int ymode;              // kYAdd, kYAddB, kYInit
 };
+
+// d b with its roundings fixed (d.im b.im and d.re b.im rounded before the FMA
+// of their part), whatever the compiler makes of the code around it: a term of
+// the sum has the same bits in every kernel and mode.
+template <typename T>
+__device__ __forceinline__ cpx<T> y_term(cpx<T> d, cpx<T> b) {
+    return mk(fma(d.re, b.re, -(d.im * b.im)), fma(d.im, b.re, d.re * b.im));
+}
+// The sum's terms that one application adds, in the order of separate
+// additions: y + gamma out, (y + delta b) + gamma out, or delta b + gamma out
+// (y not read).  Returns y without its last term, from y's old values yv.
+template <typename T>
+__device__ __forceinline__ void y_terms(const WOut &o, const cpx<T> b[12], cpx<T> yv[12]) {
+    const cpx<T> de = mk((T)o.delta.x, (T)o.delta.y);
+    if (o.ymode == kYInit) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) yv[k] = y_term(de, b[k]);
+    } else if (o.ymode == kYAddB) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) yv[k] = yv[k] + y_term(de, b[k]);
+    }
+}
 
 // Occupancy targets (minimum wavefronts per SIMD the register allocation must
 // allow).  The uniform kernels come in two targets chosen by the autotuner:
@@ -605,9 +628,9 @@ __device__ __forceinline__ void wilson_site(const WIn<P> in, const WOut o, long 
     const cpx<T> be = mk((T)o.beta.x, (T)o.beta.y);
     const cpx<T> beg5 = o.theta ? mk(-be.re, -be.im) : be;   // Theta = gamma5 flips spins 2, 3
     const SiteAcc<P, UNI> B(in.b, in.bsc, s, N, (uint32_t)r);
-    cpx<T> res[12];
+    cpx<T> bv[12], res[12];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) res[k] = B.ld(k);
+    for (int k = 0; k < 12; ++k) bv[k] = B.ld(k);
     if (o.a && !o.a_is_b) {
         const SiteAcc<P, UNI> A(o.a, o.asc, s, N, (uint32_t)r);
         cpx<T> av[12];
@@ -615,14 +638,14 @@ __device__ __forceinline__ void wilson_site(const WIn<P> in, const WOut o, long 
         for (int k = 0; k < 12; ++k) av[k] = A.ld(k);
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            const cpx<T> mb = res[k] - kap * acc[k / 3][k % 3];
+            const cpx<T> mb = bv[k] - kap * acc[k / 3][k % 3];
             res[k] = (k >= 6 ? beg5 : be) * mb + al * av[k];
         }
     } else {
 #pragma unroll
         for (int k = 0; k < 12; ++k) {
-            const cpx<T> mb = res[k] - kap * acc[k / 3][k % 3];
-            res[k] = (k >= 6 ? beg5 : be) * mb + al * res[k];
+            const cpx<T> mb = bv[k] - kap * acc[k / 3][k % 3];
+            res[k] = (k >= 6 ? beg5 : be) * mb + al * bv[k];
         }
     }
     if constexpr (P == MPMC_FP16S) {
@@ -641,17 +664,22 @@ __device__ __forceinline__ void wilson_site(const WIn<P> in, const WOut o, long 
         for (int k = 0; k < 12; ++k) d[(s * 12 + k) * N + r] = __floats2half2_rn(res[k].re * inv, res[k].im * inv);
         o.osc[s * N + r] = mx;
     } else {
-        const SiteAcc<P, UNI> O(o.out, nullptr, s, N, (uint32_t)r);
+        if (o.out) {
+            const SiteAcc<P, UNI> O(o.out, nullptr, s, N, (uint32_t)r);
 #pragma unroll
-        for (int k = 0; k < 12; ++k) O.st(k, res[k]);
+            for (int k = 0; k < 12; ++k) O.st(k, res[k]);
+        }
         if (o.y) {
             const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
             const SiteAcc<P, UNI> Y(o.y, nullptr, s, N, (uint32_t)r);
             cpx<T> yv[12];
+            if (o.ymode != kYInit) {
 #pragma unroll
-            for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+            }
+            y_terms(o, bv, yv);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + ga * res[k]);
+            for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + y_term(ga, res[k]));
         }
     }
 }
@@ -761,13 +789,9 @@ __device__ __forceinline__ T group8_sum1(T v) {
 template <typename T>
 __device__ __forceinline__ cpx<T> group8_sum(cpx<T> v) { return mk(group8_sum1(v.re), group8_sum1(v.im)); }
 
-// yinit_on: y = yinit * b + gamma * out instead of y += gamma * out (the
-// first step of a polynomial, whose accumulator starts at b / theta_1; needs
-// a == b), y is then not read.
 template <int P>
 __global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, const int *__restrict__ nbr,
-                                                 const typename LinkT<P>::type *__restrict__ links, WOut o, long V,
-                                                 double2 yinit, int yinit_on) {
+                                                 const typename LinkT<P>::type *__restrict__ links, WOut o, long V) {
     using T = typename Store<P>::real;
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const long s = t >> 3;
@@ -784,7 +808,7 @@ __global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, con
     for (int k = 0; k < 12; ++k) {
         bt[k] = epi ? mk((T)sp[k].x, (T)sp[k].y) : mk(T(0), T(0));
         av[k] = epi && has_a ? mk((T)ap[k].x, (T)ap[k].y) : mk(T(0), T(0));
-        yv[k] = epi && o.y && !yinit_on ? mk((T)yp[k].x, (T)yp[k].y) : mk(T(0), T(0));
+        yv[k] = epi && o.y && o.ymode != kYInit ? mk((T)yp[k].x, (T)yp[k].y) : mk(T(0), T(0));
     }
     cpx<T> c[12];
 #pragma unroll
@@ -844,17 +868,20 @@ __global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, con
     const cpx<T> al = mk((T)o.alpha.x, (T)o.alpha.y);
     const cpx<T> be = mk((T)o.beta.x, (T)o.beta.y);
     const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
-    const cpx<T> yi = mk((T)yinit.x, (T)yinit.y);
+    const cpx<T> de = mk((T)o.delta.x, (T)o.delta.y);
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
         cpx<T> mb = bt[k] - kap * c[k];
         if (o.theta && k >= 6) mb = mk(-mb.re, -mb.im);
         cpx<T> v = be * mb;
         if (has_a) v = v + al * av[k];
-        op[k].x = v.re;
-        op[k].y = v.im;
+        if (o.out) {
+            op[k].x = v.re;
+            op[k].y = v.im;
+        }
         if (o.y) {
-            const cpx<T> yn = (yinit_on ? yi * av[k] : yv[k]) + ga * v;
+            const cpx<T> yb = o.ymode == kYAdd ? yv[k] : o.ymode == kYInit ? y_term(de, bt[k]) : yv[k] + y_term(de, bt[k]);
+            const cpx<T> yn = yb + y_term(ga, v);   // as y_terms
             yp[k].x = yn.re;
             yp[k].y = yn.im;
         }
@@ -869,8 +896,7 @@ __global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, con
 // 16-byte loads, and an FP32 link as four 16-byte loads and one 8-byte load
 // (link mu of a site starts 72 mu bytes into the site's 288, so its 16-byte
 // alignment is known from mu at compile time).  The hop arithmetic is the
-// generic kernel's (apply), so M b is the same bit for bit; the accumulator
-// start y = yinit b of a polynomial's first step is fused into the epilogue.
+// generic kernel's (apply), so M b is the same bit for bit.
 // Site indices are 32-bit here (the library keeps V below 2^31): the
 // neighbour offset is a select between two constants, so no branch splits the
 // hops (a branch would let the compiler sink each hop's arithmetic below the
@@ -987,7 +1013,7 @@ __device__ __forceinline__ void sv_store12(void *p, int s, const cpx<typename St
 template <int P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == MPMC_FP64 ? 2 : 3))) void k_wilson_sv(const void *__restrict__ b,
                                                    const typename LinkT<P>::type *__restrict__ links, WOut o,
-                                                   SvGeom G, long V, double2 yinit, int yinit_on) {
+                                                   SvGeom G, long V) {
     using T = typename Store<P>::real;
     const unsigned su = xcd_tile(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
     if (su >= (unsigned)V) return;
@@ -1036,19 +1062,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == MPMC_F
             res[k] = (k >= 6 ? beg5 : be) * mb + al * bv[k];
         }
     }
-    sv_store12<P>(o.out, s, res);
+    if (o.out) sv_store12<P>(o.out, s, res);
     if (o.y) {
         const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
         cpx<T> yv[12];
-        if (yinit_on) {   // y = yinit b + gamma out (b is also the additive operand here)
-            const cpx<T> yi = mk((T)yinit.x, (T)yinit.y);
+        if (o.ymode != kYInit) sv_load12<P>(o.y, s, yv);
+        y_terms(o, bv, yv);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) yv[k] = yi * bv[k] + ga * res[k];
-        } else {
-            sv_load12<P>(o.y, s, yv);
-#pragma unroll
-            for (int k = 0; k < 12; ++k) yv[k] = yv[k] + ga * res[k];
-        }
+        for (int k = 0; k < 12; ++k) yv[k] = yv[k] + y_term(ga, res[k]);
         sv_store12<P>(o.y, s, yv);
     }
 }
@@ -1538,16 +1559,22 @@ __global__ __launch_bounds__(256 * TZ) __attribute__((amdgpu_waves_per_eu(2))) v
             for (int k = 0; k < 12; ++k) {
                 const cpx<T> mb = cur[k] - kap * acc[k / 3][k % 3];
                 res[k] = (k >= 6 ? beg5 : be) * mb + al * av[k];
-                O.st_stream(k, res[k]);
+            }
+            if (o.out) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) O.st_stream(k, res[k]);
             }
             if (o.y) {
                 const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
                 const SiteAcc<MPMC_FP32, true> Y(o.y, nullptr, s, N, r);
                 cpx<T> yv[12];
+                if (o.ymode != kYInit) {
 #pragma unroll
-                for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                    for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                }
+                y_terms(o, cur, yv);
 #pragma unroll
-                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + ga * res[k]);
+                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + y_term(ga, res[k]));
             }
         } else {
             const cpx<T> ccf = mk((T)c.x, (T)c.y);
@@ -1864,16 +1891,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void k
             for (int k = 0; k < 12; ++k) {
                 const cpx<T> mb = cur[k] - kap * acc[k / 3][k % 3];
                 res[k] = (k >= 6 ? beg5 : be) * mb + al * av[k];
-                O.st_stream(k, res[k]);
+            }
+            if (o.out) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) O.st_stream(k, res[k]);
             }
             if (o.y) {
                 const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
                 const PairAcc Y(o.y, sp, vo, range, N);
                 cpx<T> yv[12];
+                if (o.ymode != kYInit) {
 #pragma unroll
-                for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                    for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                }
+                y_terms(o, cur, yv);
 #pragma unroll
-                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + ga * res[k]);
+                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + y_term(ga, res[k]));
             }
         } else {
             const cpx<T> ccf = mk((T)c.x, (T)c.y);
@@ -2117,16 +2150,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int k = 0; k < 12; ++k) {
                 const cpx<T> mb = cur[k] - kap * acc[k / 3][k % 3];
                 res[k] = (k >= 6 ? beg5 : be) * mb + al * av[k];
-                O.st_stream(k, res[k]);
+            }
+            if (o.out) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) O.st_stream(k, res[k]);
             }
             if (o.y) {
                 const cpx<T> ga = mk(o.gamma.x, o.gamma.y);
                 const SiteAcc<MPMC_FP64, true> Y(o.y, nullptr, s, N, r);
                 cpx<T> yv[12];
+                if (o.ymode != kYInit) {
 #pragma unroll
-                for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                    for (int k = 0; k < 12; ++k) yv[k] = Y.ld(k);
+                }
+                y_terms(o, cur, yv);
 #pragma unroll
-                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + ga * res[k]);
+                for (int k = 0; k < 12; ++k) Y.st(k, yv[k] + y_term(ga, res[k]));
             }
         } else {
             const cpx<T> ccf = mk(c.x, c.y);
@@ -2347,7 +2386,7 @@ static SvGeom sv_geom(const mpmc_ctx *ctx) {
 }
 
 template <int P>
-static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs, double2 yinit, int yinit_on) {
+static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
     const long work = ctx->V * nrhs;
     const unsigned grid = grid_for(work, 256);
     WIn<P> in = make_in<P>(ctx, b, nrhs);
@@ -2355,18 +2394,15 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs, double2 yi
         if (nrhs == 1) {
             const int sv = single_vector_kernel(ctx, P);
             if (sv == 0) {
-                k_wilson1<P><<<grid_for(ctx->V * 8, 64), 64, 0, ctx->stream>>>(in.b, in.nbr, in.links, o, ctx->V,
-                                                                                yinit, yinit_on);
+                k_wilson1<P><<<grid_for(ctx->V * 8, 64), 64, 0, ctx->stream>>>(in.b, in.nbr, in.links, o, ctx->V);
                 return;
             }
             if (sv == 2) {
                 k_wilson_sv<P><<<grid_for(ctx->V, 256), 256, 0, ctx->stream>>>(in.b, in.links, o, sv_geom(ctx),
-                                                                               ctx->V, yinit, yinit_on);
+                                                                               ctx->V);
                 return;
             }
-            // site per lane (the generic kernel below); the accumulator start
-            // y = yinit b is its own pass
-            if (yinit_on) blas_axpby(ctx, b, o.y, 1, P, yinit, make_double2(0, 0));
+            // site per lane: the generic kernel below
         }
     }
     if constexpr (P == MPMC_FP32) {
@@ -2422,13 +2458,12 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs, double2 yi
 }
 
 int wilson_launch_full(mpmc_ctx *ctx, const void *b, const void *a, void *out, void *y, int nrhs, int prec,
-                       double2 alpha, double2 beta, double2 gamma, int dagger, int theta, double2 yinit,
-                       int yinit_on) {
+                       double2 alpha, double2 beta, double2 gamma, int dagger, int theta, double2 delta,
+                       int ymode) {
     if (prec == MPMC_FP16S && y) return set_err(ctx, MPMC_EINVAL, "FP16S output cannot accumulate");
-    if (yinit_on && (nrhs != 1 || !y || a != b))
-        return set_err(ctx, MPMC_EINVAL, "accumulator start from the operand: single vectors with a == b only");
+    if ((ymode != kYAdd || !out) && !y) return set_err(ctx, MPMC_EINVAL, "operator: no output");
     WOut o;
-    VecRef vo = vref(ctx, out, nrhs, prec);
+    VecRef vo = out ? vref(ctx, out, nrhs, prec) : VecRef{nullptr, nullptr};
     o.out = vo.d;
     o.osc = vo.sc;
     VecRef va = a ? vref(ctx, a, nrhs, prec) : VecRef{nullptr, nullptr};
@@ -2440,22 +2475,24 @@ int wilson_launch_full(mpmc_ctx *ctx, const void *b, const void *a, void *out, v
     o.alpha = alpha;
     o.beta = beta;
     o.gamma = gamma;
+    o.delta = delta;
+    o.ymode = ymode;
     o.g = dagger ? -1.f : 1.f;
     o.theta = theta;
     o.out_fp32 = 0;
     const int ev = nrhs > 1 ? timing_begin(ctx) : -1;   // single vectors: counted, no events
-    if (prec == MPMC_FP64) launch_w<MPMC_FP64>(ctx, b, o, nrhs, yinit, yinit_on);
-    else if (prec == MPMC_FP32) launch_w<MPMC_FP32>(ctx, b, o, nrhs, yinit, yinit_on);
-    else launch_w<MPMC_FP16S>(ctx, b, o, nrhs, yinit, yinit_on);
+    if (prec == MPMC_FP64) launch_w<MPMC_FP64>(ctx, b, o, nrhs);
+    else if (prec == MPMC_FP32) launch_w<MPMC_FP32>(ctx, b, o, nrhs);
+    else launch_w<MPMC_FP16S>(ctx, b, o, nrhs);
     HIP_OR_RET(ctx, hipGetLastError());
     if (ctx->timing) {
         // algorithmic bytes: operand read once, a read once if distinct,
         // out written once, y read (unless it starts from b) and written,
         // links once per site
         const double sb = spinor_bytes(prec);
-        double per = 2 * sb;
+        double per = out ? 2 * sb : sb;
         if (a && a != b) per += sb;
-        if (y) per += yinit_on ? sb : 2 * sb;
+        if (y) per += ymode == kYInit ? sb : 2 * sb;
         const double bytes = (double)ctx->V * ((double)nrhs * per + link_bytes(prec));
         if (ev >= 0) timing_end(ctx, ev, prec | MPMC_TIMING_PLAIN, bytes);
         else timing_count(ctx, prec | MPMC_TIMING_SINGLE, bytes);
@@ -2472,6 +2509,8 @@ int wilson_apply_h2f(mpmc_ctx *ctx, const void *b, void *out, int nrhs) {
     o.asc = nullptr;
     o.a_is_b = 0;
     o.y = nullptr;
+    o.delta = make_double2(0, 0);
+    o.ymode = kYAdd;
     o.kappa = ctx->kappa;
     o.alpha = make_double2(0, 0);
     o.beta = make_double2(1, 0);
@@ -2480,7 +2519,7 @@ int wilson_apply_h2f(mpmc_ctx *ctx, const void *b, void *out, int nrhs) {
     o.theta = 0;
     o.out_fp32 = 1;
     const int ev = timing_begin(ctx);
-    launch_w<MPMC_FP16S>(ctx, b, o, nrhs, make_double2(0, 0), 0);
+    launch_w<MPMC_FP16S>(ctx, b, o, nrhs);
     HIP_OR_RET(ctx, hipGetLastError());
     if (ev >= 0)
         timing_end(ctx, ev, MPMC_FP16S | MPMC_TIMING_PLAIN,
