@@ -156,8 +156,31 @@ __global__ __launch_bounds__(256) void k_dcgs_dots(const void *__restrict__ V, s
 // vectors over it.  u and z are read once per step (the row form above reads
 // them once per group of kDcgsJB vectors); per-wavefront sums wait in LDS
 // until one barrier at the end.  A 16-byte slot holds two FP32 or one FP64
-// complex element.
+// complex element.  Bound by the reads of the basis; the wavefront's sums cost
+// as much as they did where every value had its own chain of six exchanges, so
+// two vectors are summed together (wave_scatter_sum, 9 exchanges instead of
+// 48): 16^4 FP64, 17 vectors 66 -> 40.5 us (5.9 TB/s); four at a time hold too
+// many loads for the wavefronts to be as many (55 us).
 constexpr int kDcgsRunMaxV = 256;   // basis vectors the LDS of the run form holds
+
+// Sums of M values over the wavefront, M a power of two up to 32: each
+// exchange halves the values a lane holds, so all of them take M - 1 exchanges
+// and log2(64 / M) more, not 6 M.  v[0] of lane l ends as the sum of v[l / (64 / M)].
+template <int M>
+__device__ __forceinline__ void wave_scatter_sum(double *v, int lane) {
+    int o = 32;
+#pragma unroll
+    for (int h = M / 2; h > 0; h >>= 1, o >>= 1) {
+        const bool up = (lane & o) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const double keep = up ? v[i + h] : v[i], send = up ? v[i] : v[i + h];
+            v[i] = keep + __shfl_xor(send, o);
+        }
+    }
+#pragma unroll
+    for (int q = 32 / M; q > 0; q >>= 1) v[0] += __shfl_xor(v[0], q);
+}
 
 template <int P>
 struct Slot;
@@ -181,7 +204,7 @@ __global__ __launch_bounds__(256) void k_dcgs_dots_run(const void *__restrict__ 
                                                        const void *__restrict__ u, const void *__restrict__ z,
                                                        long nslots, double2 *__restrict__ partial, int NB) {
     using R = typename Slot<P>::raw;
-    constexpr int E = Slot<P>::per;
+    constexpr int E = Slot<P>::per, G = 2;
     __shared__ double2 red[2 * kDcgsRunMaxV + 2][4];
     const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
     const long base = (long)blockIdx.x * 256 * S + threadIdx.x;
@@ -200,29 +223,36 @@ __global__ __launch_bounds__(256) void k_dcgs_dots_run(const void *__restrict__ 
             ba = ba + conjmul(ue, ze);
         }
     }
-    for (int q = 0; q < nv; ++q) {
-        const R *vq = reinterpret_cast<const R *>((const char *)V + (size_t)q * vstep);
-        R vr[S];
+    for (int q0 = 0; q0 < nv; q0 += G) {
+        R vr[G][S];
 #pragma unroll
-        for (int k = 0; k < S; ++k) {   // loads issued together
-            const long sl = base + (long)k * 256;
-            vr[k] = sl < nslots ? vq[sl] : R{};
+        for (int g = 0; g < G; ++g) {   // loads issued together; past the last vector it is read again
+            const R *vq = reinterpret_cast<const R *>((const char *)V + (size_t)min(q0 + g, nv - 1) * vstep);
+#pragma unroll
+            for (int k = 0; k < S; ++k) vr[g][k] = vq[min(base + (long)k * 256, nslots - 1)];
         }
-        cpx<double> sa = mk(0.0, 0.0), ta = mk(0.0, 0.0);
+        double s[4 * G];   // V^H u and V^H z of each vector
 #pragma unroll
-        for (int k = 0; k < S; ++k)
+        for (int g = 0; g < G; ++g) {
+            cpx<double> sa = mk(0.0, 0.0), ta = mk(0.0, 0.0);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const cpx<double> ve = Slot<P>::el(vr[k], e);
-                sa = sa + conjmul(ve, Slot<P>::el(ur[k], e));
-                ta = ta + conjmul(ve, Slot<P>::el(zr[k], e));
-            }
-        const double2 a = wave_sum2(make_double2(sa.re, sa.im));
-        const double2 b = wave_sum2(make_double2(ta.re, ta.im));
-        if (ln == 0) {
-            red[q][wv] = a;
-            red[nv + q][wv] = b;
+            for (int k = 0; k < S; ++k)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {   // u and z are zero past the end
+                    const cpx<double> ve = Slot<P>::el(vr[g][k], e);
+                    sa = sa + conjmul(ve, Slot<P>::el(ur[k], e));
+                    ta = ta + conjmul(ve, Slot<P>::el(zr[k], e));
+                }
+            s[4 * g + 0] = sa.re;
+            s[4 * g + 1] = sa.im;
+            s[4 * g + 2] = ta.re;
+            s[4 * g + 3] = ta.im;
         }
+        // lane l ends with the wavefront's sum of s[l / (64 / 4G)]
+        wave_scatter_sum<4 * G>(s, ln);
+        constexpr int W = 64 / (4 * G);
+        const int q = q0 + ln / (4 * W), c = ln / W % 4;
+        if (ln % W == 0 && q < nv) reinterpret_cast<double *>(&red[(c >> 1) * nv + q][wv])[c & 1] = s[0];
     }
     const double2 a2 = wave_sum2(make_double2(aa.re, aa.im)), b2 = wave_sum2(make_double2(ba.re, ba.im));
     if (ln == 0) {
@@ -264,12 +294,18 @@ __global__ __launch_bounds__(256) void k_dcgs_reduce(const double2 *__restrict__
     }
 }
 
-__device__ __forceinline__ double block_sum1(double v, double *red4) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+constexpr int kCoefThreads = 1024;
+// sums of v[0..3] over the workgroup, to every thread
+__device__ __forceinline__ void block_sum4(double v[4], double (*red)[4]) {
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+    wave_scatter_sum<4>(v, ln);
+    if (ln % 16 == 0) red[wv][ln / 16] = v[0];
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red4[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return red4[0] + red4[1] + red4[2] + red4[3];
+    for (int c = 0; c < 4; ++c) v[c] = 0.0;
+#pragma unroll 4
+    for (int w = 0; w < kCoefThreads / 64; ++w)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] += red[w][c];
 }
 
 // Coefficients of step j from D (k_dcgs_reduce; nv = j basis vectors): the
@@ -277,57 +313,52 @@ __device__ __forceinline__ double block_sum1(double v, double *red4) {
 // in CGS2: nu <= 1e-14 ||H||_F), then (unless last) the single-projection
 // column j and C = [1/nu, -c/nu^2, 1/nu, -s_i/nu (i < j), -(t_i - s_i c/nu)/nu
 // (i < j)].  After a breakdown every coefficient is 0 (later vectors stay 0).
-// j = 0 also records ||b|| = nu in state[2].  ldh = d + 1; j <= d <= 500.
-__global__ __launch_bounds__(256) void k_dcgs_coef(const double2 *__restrict__ D, int j, int ldh,
-                                                   double2 *__restrict__ H, double *__restrict__ state,
-                                                   double2 *__restrict__ C, int last) {
-    __shared__ double2 sv[512], tv[512];
-    __shared__ double red4[4];
+// j = 0 also records ||b|| = nu in state[2].  ldh = d + 1; j <= d <= 500.  One
+// workgroup and a chain of waits: the four sums take one exchange and barrier,
+// and sixteen wavefronts share the columns of H s: 4.6 us at 33 steps (9 us with
+// four wavefronts, a barrier pair per sum and a row per thread).
+__global__ __launch_bounds__(kCoefThreads) void k_dcgs_coef(const double2 *__restrict__ D, int j, int ldh,
+                                                            double2 *__restrict__ H, double *__restrict__ state,
+                                                            double2 *__restrict__ C, int last) {
+    __shared__ double2 sv[512], tv[512], gp[kCoefThreads];
+    __shared__ double red[kCoefThreads / 64][4];
     __shared__ double sh_nu;
     __shared__ int sh_bad;
     const int tid = threadIdx.x;
-    for (int i = tid; i < j; i += 256) {
-        sv[i] = D[i];
-        tv[i] = D[j + i];
-    }
-    __syncthreads();
     const double2 a = D[2 * j], b = D[2 * j + 1];
-    double ss = 0.0, stre = 0.0, stim = 0.0;
-    for (int i = tid; i < j; i += 256) {
-        ss += sv[i].x * sv[i].x + sv[i].y * sv[i].y;
-        stre += sv[i].x * tv[i].x + sv[i].y * tv[i].y;   // s^H t
-        stim += sv[i].x * tv[i].y - sv[i].y * tv[i].x;
-    }
-    ss = block_sum1(ss, red4);
-    stre = block_sum1(stre, red4);
-    stim = block_sum1(stim, red4);
-    const double nu = sqrt(fmax(a.x - ss, 0.0));
-    // the final column j-1 and its share of the running Frobenius norm
-    double col = 0.0;
-    if (j > 0) {
+    const double st0 = state[0], st1 = state[1];
+    // sums: s^H s, s^H t (re, im), the final column j-1's share of the Frobenius norm
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = tid; i < j; i += kCoefThreads) {
+        const double2 s = D[i], t = D[j + i];
         double2 *Hc = H + (size_t)(j - 1) * ldh;
-        for (int i = tid; i < j; i += 256) {
-            double2 h = Hc[i];
-            h.x += sv[i].x;
-            h.y += sv[i].y;
-            Hc[i] = h;
-            col += h.x * h.x + h.y * h.y;
-        }
+        double2 h = Hc[i];
+        sv[i] = s;
+        tv[i] = t;
+        h.x += s.x;
+        h.y += s.y;
+        Hc[i] = h;
+        sum[0] += s.x * s.x + s.y * s.y;
+        sum[1] += s.x * t.x + s.y * t.y;
+        sum[2] += s.x * t.y - s.y * t.x;
+        sum[3] += h.x * h.x + h.y * h.y;
     }
-    col = block_sum1(col, red4);
+    block_sum4(sum, red);
+    const double ss = sum[0], stre = sum[1], stim = sum[2], col = sum[3];
+    const double nu = sqrt(fmax(a.x - ss, 0.0));
     if (tid == 0) {
-        bool bad = state[1] >= 0 || !(nu == nu);
+        bool bad = st1 >= 0 || !(nu == nu);
         if (j == 0) {
             state[2] = nu;
             if (!(nu > 0)) bad = true;
         } else {
-            const double fro = state[0] + col + nu * nu;
+            const double fro = st0 + col + nu * nu;
             state[0] = fro;
             if (!bad && nu <= 1e-14 * sqrt(fro)) bad = true;
-            if (bad && state[1] < 0) state[1] = j;
+            if (bad && st1 < 0) state[1] = j;
             H[(size_t)(j - 1) * ldh + j] = make_double2(bad ? 0.0 : nu, 0.0);
         }
-        if (bad && j == 0 && state[1] < 0) state[1] = 0;
+        if (bad && j == 0 && st1 < 0) state[1] = 0;
         sh_nu = nu;
         sh_bad = bad ? 1 : 0;
     }
@@ -341,7 +372,7 @@ __global__ __launch_bounds__(256) void k_dcgs_coef(const double2 *__restrict__ D
         C[1] = make_double2(-c.re * inu * inu, -c.im * inu * inu);
         C[2] = make_double2(last ? 0.0 : inu, 0.0);
     }
-    for (int i = tid; i < j; i += 256) {
+    for (int i = tid; i < j; i += kCoefThreads) {
         C[3 + i] = make_double2(-sv[i].x * inu, -sv[i].y * inu);
         // t_i - s_i c / nu
         const double r = tv[i].x - (sv[i].x * c.re - sv[i].y * c.im) * inu;
@@ -350,20 +381,35 @@ __global__ __launch_bounds__(256) void k_dcgs_coef(const double2 *__restrict__ D
     }
     if (last) return;
     // single-projection column j: h_i = (t_i - g_i) / nu (i < j), h_j = (c - g_j) / nu,
-    // g = H(0:j, 0:j-1) s.  Row i per thread, all k: the entries below the
-    // subdiagonal are zero (H starts zeroed), so the loop bound is uniform and
-    // the loads of one k are one coalesced column segment.
+    // g = H(0:j, 0:j-1) s.  64 rows at a time, the columns k dealt to the 16
+    // wavefronts: the entries below the subdiagonal are zero (H starts zeroed),
+    // so the bounds are uniform and a load is one coalesced column segment.
     double2 *Hj = H + (size_t)j * ldh;
-    for (int i = tid; i <= j; i += 256) {
+    constexpr int KP = kCoefThreads / 64;
+    const int ln = tid & 63, kp = tid >> 6;
+    for (int i0 = 0; i0 <= j; i0 += 64) {
+        const int i = i0 + ln;
         double gr = 0.0, gi = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < j; ++k) {
-            const double2 h = H[(size_t)k * ldh + i];
-            gr += h.x * sv[k].x - h.y * sv[k].y;
-            gi += h.x * sv[k].y + h.y * sv[k].x;
+        if (i <= j) {
+#pragma unroll 4
+            for (int k = kp; k < j; k += KP) {
+                const double2 h = H[(size_t)k * ldh + i];
+                gr += h.x * sv[k].x - h.y * sv[k].y;
+                gi += h.x * sv[k].y + h.y * sv[k].x;
+            }
         }
-        const double2 tt = i < j ? tv[i] : make_double2(c.re, c.im);
-        Hj[i] = make_double2((tt.x - gr) * inu, (tt.y - gi) * inu);
+        gp[tid] = make_double2(gr, gi);
+        __syncthreads();
+        if (kp == 0 && i <= j) {
+#pragma unroll
+            for (int w = 1; w < KP; ++w) {
+                gr += gp[w * 64 + ln].x;
+                gi += gp[w * 64 + ln].y;
+            }
+            const double2 tt = i < j ? tv[i] : make_double2(c.re, c.im);
+            Hj[i] = make_double2((tt.x - gr) * inu, (tt.y - gi) * inu);
+        }
+        __syncthreads();
     }
 }
 
@@ -446,10 +492,12 @@ static int dcgs_launch_dots(mpmc_ctx *ctx, int prec, const void *V, size_t vstep
     const long n = ctx->n;
     if (nv <= kDcgsRunMaxV) {
         // run form: 8 (FP64) or 4 (FP32) slots per thread where that still gives
-        // two workgroups per compute unit (126 and 112 VGPRs), else 2
+        // every compute unit a workgroup (16^4 FP64, 33 vectors: GMRES(33) 4.77
+        // ms, 5.06 ms with 2), else 2 (12^4 FP64: 2.53 ms, 2.56 ms with 8; 8^4:
+        // 1.64 against 1.76 ms)
         const long nslots = prec == MPMC_FP64 ? n : n / 2;   // n = 12 V is even
         const int Sbig = prec == MPMC_FP64 ? 8 : 4;
-        const int S = (nslots + 256L * Sbig - 1) / (256L * Sbig) >= 2L * ctx->num_cu ? Sbig : 2;
+        const int S = (nslots + 256L * Sbig - 1) / (256L * Sbig) >= ctx->num_cu ? Sbig : 2;
         const int NB = (int)((nslots + 256L * S - 1) / (256L * S));
         double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)(2 * nv + 2) * NB * sizeof(double2));
         if (!part) return MPMC_ENOMEM;
@@ -557,12 +605,12 @@ static int arnoldi_run_dcgs2(mpmc_ctx *ctx, const OpDesc &op, void *V, double *H
         const void *cur = j == 0 ? V : u;   // the candidate for v_j (the start vector at j = 0)
         RET_IF(apply_op(ctx, op, cur, z));
         RET_IF(dcgs_launch_dots(ctx, op.prec, V, vstep, j, cur, z, D));
-        k_dcgs_coef<<<1, 256, 0, ctx->stream>>>(D, j, d + 1, (double2 *)H, state, C, 0);
+        k_dcgs_coef<<<1, kCoefThreads, 0, ctx->stream>>>(D, j, d + 1, (double2 *)H, state, C, 0);
         HIP_OR_RET(ctx, hipGetLastError());
         RET_IF(dcgs_launch_update(ctx, op.prec, V, vstep, j, cur, z, u, (char *)V + (size_t)j * vstep, C));
     }
     RET_IF(dcgs_launch_dots(ctx, op.prec, V, vstep, d, u, nullptr, D));
-    k_dcgs_coef<<<1, 256, 0, ctx->stream>>>(D, d, d + 1, (double2 *)H, state, C, 1);
+    k_dcgs_coef<<<1, kCoefThreads, 0, ctx->stream>>>(D, d, d + 1, (double2 *)H, state, C, 1);
     HIP_OR_RET(ctx, hipGetLastError());
     return dcgs_launch_update(ctx, op.prec, V, vstep, d, u, nullptr, nullptr, (char *)V + (size_t)d * vstep, C);
 }
