@@ -744,13 +744,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occ<P, true
 }
 
 // ---------------------------------------------------- single vectors --
+// Lattice geometry of the single-vector kernels, which compute the neighbours.
+struct SvGeom {
+    int L[4];
+    int st[4];     // site strides 1, Lx, Lx Ly, Lx Ly Lz
+    int wrap[4];   // (L_mu - 1) st_mu
+    unsigned inv[3];   // floor(2^32 / L_mu)
+    int anti;      // antiperiodic in t
+};
+
 // nrhs == 1 (GMRES-polynomial and deflation Arnoldi cycles): eight lanes per
-// site, one hop each, so a single-vector matvec occupies 8x more wavefronts;
-// the eight 12-component contributions are summed with DPP (quad xor 1 and 2,
-// then row_shr 4, which leaves the site's total in lane 4 of its group), and
-// lane 4 loads the epilogue operands before the hop, so they arrive while
-// the hop computes.  Workgroups are one wavefront: an 8^4 vector is 32,768
-// threads, which 256-thread workgroups would put on half the compute units.
+// site, one hop each, so a single-vector matvec occupies 8x more wavefronts.
+// Bound by a chain of latencies on small lattices: one load (the neighbour
+// follows from the site's coordinates, no table), the hop, the sum over the
+// eight lanes, the store.  The sum halves the components with each exchange,
+// so four lanes finish three components each, and every lane's operands are
+// unconditional loads issued with the hop's (a lane with all twelve of the
+// site's needed 36 loads behind branches and held 246 registers, 132 now).
+// Workgroups are one wavefront: an 8^4 vector is 32,768 threads, which
+// 256-thread workgroups would put on half the compute units; consecutive ones
+// run on one XCD, whose L2 then serves the neighbours.  A step of a polynomial:
+// 8^4 FP64 5.9 -> 4.1 us, FP32 5.4 -> 3.3 us; 12^4 FP64 17.1 -> 8.4 us; 24^4
+// FP64 105 us, FP32 46 us (3.0 and 3.5 TB/s of algorithmic bytes).
 template <typename T>
 __device__ __forceinline__ cpx<T> mulc_rt(cpx<T> z, int code) {
     T a = z.re, b = z.im;
@@ -777,119 +792,168 @@ __device__ __forceinline__ double dpp_t(double v) {
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, false);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
 }
-// Sum over the 8-lane group: quad_perm [1,0,3,2] and [2,3,0,1] (every lane of
-// a quad holds the quad's sum), then row_shr 4: lanes 4..7 of the group (and
-// 12..15 of the next, within the same 16-lane row) add the first quad.
-template <typename T>
-__device__ __forceinline__ T group8_sum1(T v) {
-    v += dpp_t<0xB1>(v);
-    v += dpp_t<0x4E>(v);
-    return v + dpp_t<0x114>(v);
+// a + (the DPP partner's a) where up is false, b + (its b) where it is true
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_exchange1(bool up, T a, T b) {
+    return (up ? b : a) + dpp_t<CTRL>(up ? a : b);
 }
-template <typename T>
-__device__ __forceinline__ cpx<T> group8_sum(cpx<T> v) { return mk(group8_sum1(v.re), group8_sum1(v.im)); }
+template <int CTRL, typename T>
+__device__ __forceinline__ cpx<T> dpp_exchange(bool up, cpx<T> a, cpx<T> b) {
+    return mk(dpp_exchange1<CTRL>(up, a.re, b.re), dpp_exchange1<CTRL>(up, a.im, b.im));
+}
 
 template <int P>
-__global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, const int *__restrict__ nbr,
-                                                 const typename LinkT<P>::type *__restrict__ links, WOut o, long V) {
+__global__ __launch_bounds__(64) void k_wilson1(const void *__restrict__ b,
+                                                const typename LinkT<P>::type *__restrict__ links, WOut o, SvGeom G,
+                                                long V) {
     using T = typename Store<P>::real;
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long s = t >> 3;
-    const int h = (int)(t & 7);
-    const bool live = s < V;
-    const bool epi = live && h == 4;   // the lane that finishes the site
-    const typename Elem<P>::type *sp = reinterpret_cast<const typename Elem<P>::type *>(b) + s * 12;
-    const typename Elem<P>::type *ap = reinterpret_cast<const typename Elem<P>::type *>(o.a_is_b ? b : o.a) + s * 12;
-    typename Elem<P>::type *yp = reinterpret_cast<typename Elem<P>::type *>(o.y) + s * 12;
-    typename Elem<P>::type *op = reinterpret_cast<typename Elem<P>::type *>(o.out) + s * 12;
-    const bool has_a = o.a_is_b || o.a;
-    cpx<T> bt[12], av[12], yv[12];
+    using E = typename Elem<P>::type;
+    const long t = (long)xcd_tile(blockIdx.x, gridDim.x) * 64 + threadIdx.x;
+    const bool live = (t >> 3) < V;
+    const long s = live ? t >> 3 : V - 1;
+    const int h = (int)(t & 7), mu = h & 3;
+    const bool fwd = h < 4;
+    // the hop's neighbour and antiperiodic sign, from the site's coordinates
+    unsigned q = (unsigned)s, x = 0;
+    int st = 0, L = 1;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        bt[k] = epi ? mk((T)sp[k].x, (T)sp[k].y) : mk(T(0), T(0));
-        av[k] = epi && has_a ? mk((T)ap[k].x, (T)ap[k].y) : mk(T(0), T(0));
-        yv[k] = epi && o.y && o.ymode != kYInit ? mk((T)yp[k].x, (T)yp[k].y) : mk(T(0), T(0));
+    for (int m = 0; m < 4; ++m) {
+        unsigned r = q;
+        if (m < 3) {
+            const unsigned Lm = (unsigned)G.L[m];
+            unsigned qn = __umulhi(q, G.inv[m]);   // the quotient or one less
+            r = q - qn * Lm;
+            const bool more = r >= Lm;
+            r = more ? r - Lm : r;
+            q = more ? qn + 1u : qn;
+        }
+        x = m == mu ? r : x;
+        st = m == mu ? G.st[m] : st;
+        L = m == mu ? G.L[m] : L;
+    }
+    const bool wrap = x == (fwd ? (unsigned)L - 1u : 0u);
+    const int off = wrap ? (L - 1) * st : -st;
+    const long sn = s + (fwd ? -off : off);
+    const T bsign = (mu == 3 && G.anti && wrap) ? T(-1) : T(1);
+    const E *bp = reinterpret_cast<const E *>(b) + sn * 12;
+    const typename LinkT<P>::type *lk = links + ((fwd ? s : sn) * 4 + mu) * 9;
+    cpx<T> psi[12], lu[9];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) psi[k] = mk((T)bp[k].x, (T)bp[k].y);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) lu[i] = mk((T)lk[i].x, (T)lk[i].y);
+    // the epilogue's operands: components k0 .. k0 + 2 of the site
+    const int k0 = 6 * (h & 1) + 3 * ((h >> 1) & 1);
+    const long e0 = s * 12 + k0;
+    const bool has_a = o.a_is_b || o.a;
+    cpx<T> bt[3], av[3], yv[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const E v = reinterpret_cast<const E *>(b)[e0 + k];
+        bt[k] = mk((T)v.x, (T)v.y);
+        av[k] = bt[k];
+        yv[k] = mk(T(0), T(0));
+    }
+    if (o.a && !o.a_is_b) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const E v = reinterpret_cast<const E *>(o.a)[e0 + k];
+            av[k] = mk((T)v.x, (T)v.y);
+        }
+    }
+    if (o.y && o.ymode != kYInit) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const E v = reinterpret_cast<const E *>(o.y)[e0 + k];
+            yv[k] = mk((T)v.x, (T)v.y);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // (1 - gamma_mu) codes: j0, c0, j1, c1, k2, d2, k3, d3 (see Proj)
+    const int j0 = mu < 2 ? 3 : 2, c0 = mu == 0 ? 3 : (mu == 1 ? 0 : (mu == 2 ? 3 : 2));
+    const int j1 = mu < 2 ? 2 : 3, c1 = mu == 0 ? 3 : (mu == 1 ? 2 : (mu == 2 ? 1 : 2));
+    const int k2 = mu < 2 ? 1 : 0, d2 = mu == 0 ? 1 : (mu == 1 ? 2 : (mu == 2 ? 1 : 2));
+    const int k3 = mu < 2 ? 0 : 1, d3 = mu == 0 ? 1 : (mu == 1 ? 0 : (mu == 2 ? 3 : 2));
+    const T sg = fwd ? T(o.g) : T(-o.g);
+    cpx<T> hh[2][3];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) {
+        const cpx<T> pj0 = j0 == 3 ? psi[9 + cc] : psi[6 + cc];
+        const cpx<T> pj1 = j1 == 3 ? psi[9 + cc] : psi[6 + cc];
+        hh[0][cc] = psi[cc] + sg * mulc_rt(pj0, c0);
+        hh[1][cc] = psi[3 + cc] + sg * mulc_rt(pj1, c1);
+    }
+    cpx<T> uh[2][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        cpx<T> t0 = mk(T(0), T(0)), t1 = mk(T(0), T(0));
+#pragma unroll
+        for (int bb = 0; bb < 3; ++bb) {
+            const cpx<T> f = lu[a * 3 + bb], r = lu[bb * 3 + a];
+            const cpx<T> u = mk(fwd ? f.re : r.re, fwd ? f.im : -r.im);
+            t0 = t0 + u * hh[0][bb];
+            t1 = t1 + u * hh[1][bb];
+        }
+        uh[0][a] = bsign * t0;
+        uh[1][a] = bsign * t1;
     }
     cpx<T> c[12];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) c[k] = mk(T(0), T(0));
-    if (live) {
-        const int mu = h & 3;
-        const bool fwd = h < 4;
-        // (1 - gamma_mu) codes: j0, c0, j1, c1, k2, d2, k3, d3 (see Proj)
-        const int j0 = mu < 2 ? 3 : 2, c0 = mu == 0 ? 3 : (mu == 1 ? 0 : (mu == 2 ? 3 : 2));
-        const int j1 = mu < 2 ? 2 : 3, c1 = mu == 0 ? 3 : (mu == 1 ? 2 : (mu == 2 ? 1 : 2));
-        const int k2 = mu < 2 ? 1 : 0, d2 = mu == 0 ? 1 : (mu == 1 ? 2 : (mu == 2 ? 1 : 2));
-        const int k3 = mu < 2 ? 0 : 1, d3 = mu == 0 ? 1 : (mu == 1 ? 0 : (mu == 2 ? 3 : 2));
-        const T sg = fwd ? T(o.g) : T(-o.g);
-        const int raw = nbr[s * 8 + h];
-        const long sn = (long)(raw & 0x7fffffff);
-        const T bsign = raw < 0 ? T(-1) : T(1);
-        const typename Elem<P>::type *bp = reinterpret_cast<const typename Elem<P>::type *>(b) + sn * 12;
-        cpx<T> psi[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) psi[k] = mk((T)bp[k].x, (T)bp[k].y);
-        cpx<T> hh[2][3];
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-            const cpx<T> pj0 = j0 == 3 ? psi[9 + cc] : psi[6 + cc];
-            const cpx<T> pj1 = j1 == 3 ? psi[9 + cc] : psi[6 + cc];
-            hh[0][cc] = psi[cc] + sg * mulc_rt(pj0, c0);
-            hh[1][cc] = psi[3 + cc] + sg * mulc_rt(pj1, c1);
-        }
-        const auto *lk = links + ((fwd ? s : sn) * 4 + mu) * 9;
-        cpx<T> uh[2][3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            cpx<T> t0 = mk(T(0), T(0)), t1 = mk(T(0), T(0));
-#pragma unroll
-            for (int bb = 0; bb < 3; ++bb) {
-                const auto lv = fwd ? lk[a * 3 + bb] : lk[bb * 3 + a];
-                const cpx<T> u = mk((T)lv.x, fwd ? (T)lv.y : (T)-lv.y);
-                t0 = t0 + u * hh[0][bb];
-                t1 = t1 + u * hh[1][bb];
-            }
-            uh[0][a] = bsign * t0;
-            uh[1][a] = bsign * t1;
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            c[a] = uh[0][a];
-            c[3 + a] = uh[1][a];
-            c[6 + a] = sg * mulc_rt(k2 ? uh[1][a] : uh[0][a], d2);
-            c[9 + a] = sg * mulc_rt(k3 ? uh[1][a] : uh[0][a], d3);
-        }
+    for (int a = 0; a < 3; ++a) {
+        c[a] = uh[0][a];
+        c[3 + a] = uh[1][a];
+        c[6 + a] = sg * mulc_rt(k2 ? uh[1][a] : uh[0][a], d2);
+        c[9 + a] = sg * mulc_rt(k3 ? uh[1][a] : uh[0][a], d3);
     }
-    // sum the eight hops of a site (lanes 8q .. 8q+7) into lane 8q + 4
+    // sum the eight hops of a site (lanes 8q .. 8q+7): each exchange halves the
+    // components a lane holds, so lane 8q + 4 + j ends with the totals of its
+    // components k0 .. k0 + 2; the tree is ((0+1)+(2+3))+((4+5)+(6+7))
+    const bool odd = h & 1, upper = h & 2;
+    cpx<T> c6[6], c3[3];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) c[k] = group8_sum(c[k]);
-    if (!epi) return;
+    for (int k = 0; k < 6; ++k) c6[k] = dpp_exchange<0xB1>(odd, c[k], c[6 + k]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c3[k] = dpp_exchange<0x4E>(upper, c6[k], c6[3 + k]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) c3[k] = mk(c3[k].re + dpp_t<0x114>(c3[k].re), c3[k].im + dpp_t<0x114>(c3[k].im));
+    if (!live || fwd) return;
     const T kap = (T)o.kappa;
     const cpx<T> al = mk((T)o.alpha.x, (T)o.alpha.y);
     const cpx<T> be = mk((T)o.beta.x, (T)o.beta.y);
-    const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y);
-    const cpx<T> de = mk((T)o.delta.x, (T)o.delta.y);
+    cpx<T> v[3];
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        cpx<T> mb = bt[k] - kap * c[k];
-        if (o.theta && k >= 6) mb = mk(-mb.re, -mb.im);
-        cpx<T> v = be * mb;
-        if (has_a) v = v + al * av[k];
-        if (o.out) {
-            op[k].x = v.re;
-            op[k].y = v.im;
+    for (int k = 0; k < 3; ++k) {
+        cpx<T> mb = bt[k] - kap * c3[k];
+        if (o.theta && odd) mb = mk(-mb.re, -mb.im);   // Theta = gamma5: spins 2 and 3
+        v[k] = be * mb;
+        if (has_a) v[k] = v[k] + al * av[k];
+    }
+    if (o.out) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            E e;
+            e.x = v[k].re;
+            e.y = v[k].im;
+            reinterpret_cast<E *>(o.out)[e0 + k] = e;
         }
-        if (o.y) {
-            const cpx<T> yb = o.ymode == kYAdd ? yv[k] : o.ymode == kYInit ? y_term(de, bt[k]) : yv[k] + y_term(de, bt[k]);
-            const cpx<T> yn = yb + y_term(ga, v);   // as y_terms
-            yp[k].x = yn.re;
-            yp[k].y = yn.im;
+    }
+    if (o.y) {
+        const cpx<T> ga = mk((T)o.gamma.x, (T)o.gamma.y), de = mk((T)o.delta.x, (T)o.delta.y);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const cpx<T> d = y_term(de, bt[k]);
+            const cpx<T> yb = o.ymode == kYAdd ? yv[k] : o.ymode == kYInit ? d : yv[k] + d;   // as y_terms
+            const cpx<T> yn = yb + y_term(ga, v[k]);
+            E e;
+            e.x = yn.re;
+            e.y = yn.im;
+            reinterpret_cast<E *>(o.y)[e0 + k] = e;
         }
     }
 }
 
-// ---------------------------------------- single vectors, large lattices --
-// One site per lane, lexicographic sites (consecutive lanes, consecutive x).
+// ---------------------------------------- single vectors, site per lane --
+// Variant 2, for the bits of a batch's column.  One site per lane, lexicographic sites (consecutive lanes, consecutive x).
 // Against the generic kernel at one right-hand side: the neighbour index and
 // the antiperiodic sign follow from the site's coordinates (no table load in
 // each hop's dependency chain), the neighbour's 12 components arrive as
@@ -901,13 +965,6 @@ __global__ __launch_bounds__(256) void k_wilson1(const void *__restrict__ b, con
 // neighbour offset is a select between two constants, so no branch splits the
 // hops (a branch would let the compiler sink each hop's arithmetic below the
 // next hops' loads and hold all eight neighbours in registers at once).
-struct SvGeom {
-    int L[4];
-    int st[4];     // site strides 1, Lx, Lx Ly, Lx Ly Lz
-    int wrap[4];   // (L_mu - 1) st_mu
-    int anti;      // antiperiodic in t
-};
-
 template <int P, int MU, bool FWD>
 __device__ __forceinline__ void fetch_sv(const void *__restrict__ b, const typename LinkT<P>::type *__restrict__ links,
                                          const SvGeom &G, int s, const int c[4], HopData<P> &H) {
@@ -2360,17 +2417,14 @@ static void launch_uniform(mpmc_ctx *ctx, const WIn<P> &in, const WOut &o, int n
                                                                           nrhs, ctx->site_order);
 }
 
-// Single vectors: k_wilson1 (eight lanes per site, one hop each, one
-// wavefront per workgroup) keeps a small lattice's dependent chain of
-// launches short; on large lattices its scattered per-lane loads dominate and
-// one site per lane (all eight hops in the lane) is faster: k_wilson_sv, or
-// the generic kernel at one right-hand side.  mpmc_tune_set(ctx, 1, prec, v)
-// pins one: v = 0 k_wilson1, 1 the generic kernel, 2 k_wilson_sv.
-constexpr long kWilson1MaxV = 20736;   // 12^4 sites
+// Single vectors take k_wilson1 on every lattice (with the table's neighbours
+// and a lane per site to finish, it lost to k_wilson_sv above 12^4 sites; now
+// 24^4 FP64 105 against 142 us, FP32 46 against 65).  mpmc_tune_set(ctx, 1, prec, v)
+// pins one: v = 0 k_wilson1, 1 the generic kernel, 2 k_wilson_sv (a lane per
+// site; the bits of a batch's column, as 1).
 static int single_vector_kernel(const mpmc_ctx *ctx, int prec) {
     const auto it = ctx->tune.find(std::make_pair(1, prec));
-    if (it != ctx->tune.end() && it->second <= 2) return it->second;
-    return ctx->V > kWilson1MaxV ? 2 : 0;
+    return it != ctx->tune.end() && it->second <= 2 ? it->second : 0;
 }
 static SvGeom sv_geom(const mpmc_ctx *ctx) {
     SvGeom G;
@@ -2379,6 +2433,7 @@ static SvGeom sv_geom(const mpmc_ctx *ctx) {
         G.L[mu] = ctx->dims[mu];
         G.st[mu] = st;
         G.wrap[mu] = (ctx->dims[mu] - 1) * st;
+        if (mu < 3) G.inv[mu] = (unsigned)((1ull << 32) / (unsigned)ctx->dims[mu] - (ctx->dims[mu] == 1 ? 1 : 0));
         st *= ctx->dims[mu];
     }
     G.anti = ctx->t_antiperiodic;
@@ -2394,7 +2449,7 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
         if (nrhs == 1) {
             const int sv = single_vector_kernel(ctx, P);
             if (sv == 0) {
-                k_wilson1<P><<<grid_for(ctx->V * 8, 64), 64, 0, ctx->stream>>>(in.b, in.nbr, in.links, o, ctx->V);
+                k_wilson1<P><<<grid_for(ctx->V * 8, 64), 64, 0, ctx->stream>>>(in.b, in.links, o, sv_geom(ctx), ctx->V);
                 return;
             }
             if (sv == 2) {
