@@ -530,8 +530,8 @@ int mpmc_set_setup_precision(mpmc_ctx *ctx, int prec);
  * V^H u, V^H (A u), u^H u and u^H A u, one more pass writes the finished
  * vector and the next candidate): two basis passes and four launches per step
  * besides the operator.  on = 1: the two projections in sequence (four basis
- * passes, eight shorter launches).  on = -1 (the default): 1 below 16^4
- * sites, where the steps are launch-bound, else 0.  EINVAL otherwise. */
+ * passes, eight shorter launches).  on = -1 (the default): as 0.  EINVAL
+ * otherwise. */
 int mpmc_set_arnoldi_cgs2(mpmc_ctx *ctx, int on);
 /* Gram-Schmidt of the inner GMRES cycles of mpmc_solve, mpmc_solve_pp,
  * mpmc_solve_batch and the solves inside mpmc_level_estimate (Sec. 3's GMRES

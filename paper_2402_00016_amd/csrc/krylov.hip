@@ -64,8 +64,6 @@ static int apply_op(mpmc_ctx *ctx, const OpDesc &op, const void *x, void *y) {
 // second operator application); each step reads the basis twice instead of
 // four times and issues four launches besides the operator instead of eight.
 
-constexpr int kDcgsJB = 8;   // basis vectors per workgroup row of the dot pass
-
 __device__ __forceinline__ double2 wave_sum2(double2 v) {
     for (int o = 32; o > 0; o >>= 1) {
         v.x += __shfl_xor(v.x, o);
@@ -75,93 +73,19 @@ __device__ __forceinline__ double2 wave_sum2(double2 v) {
 }
 
 // partial[q * NB + blk]: q < nv: V_q^H u; nv <= q < 2 nv: V_{q-nv}^H z (z may be
-// null: zero); q = 2 nv: u^H u; q = 2 nv + 1: u^H z.  Row g = blockIdx.y of the
-// grid takes basis vectors [g JB, g JB + JB); row 0 also the two u products.
-// Used above kDcgsRunMaxV basis vectors; the run form below otherwise.
-template <int P>
-__global__ __launch_bounds__(256) void k_dcgs_dots(const void *__restrict__ V, size_t vstep, int nv,
-                                                   const void *__restrict__ u, const void *__restrict__ z, long n,
-                                                   double2 *__restrict__ partial, int NB) {
-    __shared__ double2 red[2 * kDcgsJB + 2][4];
-    const int j0 = blockIdx.y * kDcgsJB;
-    cpx<double> sa[kDcgsJB], ta[kDcgsJB], aa = mk(0.0, 0.0), ba = mk(0.0, 0.0);
-#pragma unroll
-    for (int q = 0; q < kDcgsJB; ++q) sa[q] = ta[q] = mk(0.0, 0.0);
-    for (long e = (long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long)NB * 256) {
-        const auto u0 = Store<P>::ld(u, nullptr, e, 0);
-        const cpx<double> uv = mk((double)u0.re, (double)u0.im);
-        cpx<double> zv = mk(0.0, 0.0);
-        if (z) {
-            const auto z0 = Store<P>::ld(z, nullptr, e, 0);
-            zv = mk((double)z0.re, (double)z0.im);
-        }
-        if (blockIdx.y == 0) {
-            aa = aa + conjmul(uv, uv);
-            ba = ba + conjmul(uv, zv);
-        }
-        cpx<double> vq[kDcgsJB];
-#pragma unroll
-        for (int q = 0; q < kDcgsJB; ++q) {   // loads issued together, index clamped, masked below
-            const int i = j0 + q < nv ? j0 + q : (nv > 0 ? nv - 1 : 0);
-            const auto v = nv > 0 ? Store<P>::ld((const char *)V + (size_t)i * vstep, nullptr, e, 0)
-                                  : Store<P>::ld(u, nullptr, e, 0);
-            vq[q] = mk((double)v.re, (double)v.im);
-        }
-#pragma unroll
-        for (int q = 0; q < kDcgsJB; ++q)
-            if (j0 + q < nv) {
-                sa[q] = sa[q] + conjmul(vq[q], uv);
-                ta[q] = ta[q] + conjmul(vq[q], zv);
-            }
-    }
-    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-#pragma unroll
-    for (int q = 0; q < kDcgsJB; ++q) {
-        const double2 a = wave_sum2(make_double2(sa[q].re, sa[q].im));
-        const double2 b = wave_sum2(make_double2(ta[q].re, ta[q].im));
-        if (ln == 0) {
-            red[q][wv] = a;
-            red[kDcgsJB + q][wv] = b;
-        }
-    }
-    const double2 a2 = wave_sum2(make_double2(aa.re, aa.im)), b2 = wave_sum2(make_double2(ba.re, ba.im));
-    if (ln == 0) {
-        red[2 * kDcgsJB][wv] = a2;
-        red[2 * kDcgsJB + 1][wv] = b2;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 * kDcgsJB + 2) {
-        const int q = threadIdx.x;
-        double2 acc = red[q][0];
-        for (int w = 1; w < 4; ++w) {
-            acc.x += red[q][w].x;
-            acc.y += red[q][w].y;
-        }
-        long out = -1;
-        if (q < kDcgsJB) {
-            if (j0 + q < nv) out = j0 + q;
-        } else if (q < 2 * kDcgsJB) {
-            if (j0 + q - kDcgsJB < nv) out = nv + j0 + q - kDcgsJB;
-        } else if (blockIdx.y == 0) {
-            out = 2L * nv + (q - 2 * kDcgsJB);
-        }
-        if (out >= 0) partial[out * NB + blockIdx.x] = acc;
-    }
-}
-
-// The same products with the element range split instead of the basis: a
-// workgroup owns S 16-byte slots per thread (slot k of thread i at k*256 + i
+// null: zero); q = 2 nv: u^H u; q = 2 nv + 1: u^H z.
+// A workgroup owns S 16-byte slots per thread (slot k of thread i at k*256 + i
 // of the workgroup's run, so every load instruction is contiguous over the
-// wavefront), holds its run of u and z in registers, and streams all nv basis
-// vectors over it.  u and z are read once per step (the row form above reads
-// them once per group of kDcgsJB vectors); per-wavefront sums wait in LDS
-// until one barrier at the end.  A 16-byte slot holds two FP32 or one FP64
-// complex element.  Bound by the reads of the basis; the wavefront's sums cost
+// wavefront), holds its run of u and z in registers, and streams the basis
+// vectors over it: rows of the grid (blockIdx.y) take per of them each, the
+// first row also the two u products.  Per-wavefront sums wait in LDS until one
+// barrier at the end.  A 16-byte slot holds two FP32 or one FP64 complex
+// element.  Bound by the reads of the basis; the wavefront's sums cost
 // as much as they did where every value had its own chain of six exchanges, so
 // two vectors are summed together (wave_scatter_sum, 9 exchanges instead of
 // 48): 16^4 FP64, 17 vectors 66 -> 40.5 us (5.9 TB/s); four at a time hold too
 // many loads for the wavefronts to be as many (55 us).
-constexpr int kDcgsRunMaxV = 256;   // basis vectors the LDS of the run form holds
+constexpr int kDcgsRunMaxV = 256;   // basis vectors of a row: what the LDS holds
 
 // Sums of M values over the wavefront, M a power of two up to 32: each
 // exchange halves the values a lane holds, so all of them take M - 1 exchanges
@@ -202,7 +126,7 @@ struct Slot<MPMC_FP64> {
 template <int P, int S>
 __global__ __launch_bounds__(256) void k_dcgs_dots_run(const void *__restrict__ V, size_t vstep, int nv,
                                                        const void *__restrict__ u, const void *__restrict__ z,
-                                                       long nslots, double2 *__restrict__ partial, int NB) {
+                                                       long nslots, double2 *__restrict__ partial, int NB, int per) {
     using R = typename Slot<P>::raw;
     constexpr int E = Slot<P>::per, G = 2;
     __shared__ double2 red[2 * kDcgsRunMaxV + 2][4];
@@ -223,11 +147,12 @@ __global__ __launch_bounds__(256) void k_dcgs_dots_run(const void *__restrict__ 
             ba = ba + conjmul(ue, ze);
         }
     }
-    for (int q0 = 0; q0 < nv; q0 += G) {
+    const int qa = (int)blockIdx.y * per, qb = min(qa + per, nv), nq = qb - qa;   // this row's vectors
+    for (int q0 = qa; q0 < qb; q0 += G) {
         R vr[G][S];
 #pragma unroll
         for (int g = 0; g < G; ++g) {   // loads issued together; past the last vector it is read again
-            const R *vq = reinterpret_cast<const R *>((const char *)V + (size_t)min(q0 + g, nv - 1) * vstep);
+            const R *vq = reinterpret_cast<const R *>((const char *)V + (size_t)min(q0 + g, qb - 1) * vstep);
 #pragma unroll
             for (int k = 0; k < S; ++k) vr[g][k] = vq[min(base + (long)k * 256, nslots - 1)];
         }
@@ -251,22 +176,23 @@ __global__ __launch_bounds__(256) void k_dcgs_dots_run(const void *__restrict__ 
         // lane l ends with the wavefront's sum of s[l / (64 / 4G)]
         wave_scatter_sum<4 * G>(s, ln);
         constexpr int W = 64 / (4 * G);
-        const int q = q0 + ln / (4 * W), c = ln / W % 4;
-        if (ln % W == 0 && q < nv) reinterpret_cast<double *>(&red[(c >> 1) * nv + q][wv])[c & 1] = s[0];
+        const int q = q0 - qa + ln / (4 * W), c = ln / W % 4;
+        if (ln % W == 0 && q < nq) reinterpret_cast<double *>(&red[(c >> 1) * nq + q][wv])[c & 1] = s[0];
     }
     const double2 a2 = wave_sum2(make_double2(aa.re, aa.im)), b2 = wave_sum2(make_double2(ba.re, ba.im));
     if (ln == 0) {
-        red[2 * nv][wv] = a2;
-        red[2 * nv + 1][wv] = b2;
+        red[2 * nq][wv] = a2;
+        red[2 * nq + 1][wv] = b2;
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < 2 * nv + 2; q += 256) {
+    for (int q = threadIdx.x; q < (blockIdx.y == 0 ? 2 * nq + 2 : 2 * nq); q += 256) {
         double2 acc = red[q][0];
         for (int w = 1; w < 4; ++w) {
             acc.x += red[q][w].x;
             acc.y += red[q][w].y;
         }
-        partial[(long)q * NB + blockIdx.x] = acc;
+        const int row = q < nq ? qa + q : q < 2 * nq ? nv + qa + q - nq : 2 * nv + q - 2 * nq;
+        partial[(long)row * NB + blockIdx.x] = acc;
     }
 }
 
@@ -489,43 +415,31 @@ __global__ __launch_bounds__(256) void k_dcgs_update_run(const void *__restrict_
 
 static int dcgs_launch_dots(mpmc_ctx *ctx, int prec, const void *V, size_t vstep, int nv, const void *u,
                             const void *z, double2 *D) {
-    const long n = ctx->n;
-    if (nv <= kDcgsRunMaxV) {
-        // run form: 8 (FP64) or 4 (FP32) slots per thread where that still gives
-        // every compute unit a workgroup (16^4 FP64, 33 vectors: GMRES(33) 4.77
-        // ms, 5.06 ms with 2), else 2 (12^4 FP64: 2.53 ms, 2.56 ms with 8; 8^4:
-        // 1.64 against 1.76 ms)
-        const long nslots = prec == MPMC_FP64 ? n : n / 2;   // n = 12 V is even
-        const int Sbig = prec == MPMC_FP64 ? 8 : 4;
-        const int S = (nslots + 256L * Sbig - 1) / (256L * Sbig) >= ctx->num_cu ? Sbig : 2;
-        const int NB = (int)((nslots + 256L * S - 1) / (256L * S));
-        double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)(2 * nv + 2) * NB * sizeof(double2));
-        if (!part) return MPMC_ENOMEM;
-        if (prec == MPMC_FP64) {
-            if (S == 8) k_dcgs_dots_run<MPMC_FP64, 8><<<NB, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB);
-            else k_dcgs_dots_run<MPMC_FP64, 2><<<NB, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB);
-        } else {
-            if (S == 4) k_dcgs_dots_run<MPMC_FP32, 4><<<NB, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB);
-            else k_dcgs_dots_run<MPMC_FP32, 2><<<NB, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB);
-        }
-        HIP_OR_RET(ctx, hipGetLastError());
-        k_dcgs_reduce<<<2 * nv + 2, 256, 0, ctx->stream>>>(part, NB, D);
-        HIP_OR_RET(ctx, hipGetLastError());
-        return MPMC_OK;
-    }
-    const int groups = nv > 0 ? (nv + kDcgsJB - 1) / kDcgsJB : 1;
-    long nb = (long)ctx->num_cu * 8 / groups;
-    const long maxnb = (n + 255) / 256;
-    if (nb < 8) nb = 8;
-    if (nb > maxnb) nb = maxnb;
-    if (nb > 2048) nb = 2048;
-    const int NB = (int)nb;
+    // 8 (FP64) or 4 (FP32) slots per thread where that still gives every
+    // compute unit a workgroup (16^4 FP64, 33 vectors: GMRES(33) 4.77 ms, 5.06
+    // ms with 2), else 2 (12^4 FP64: 2.53 ms, 2.56 ms with 8; 8^4: 1.64 against
+    // 1.76 ms), and the basis in rows of the grid until there are four
+    // workgroups per compute unit (8^4, 129 vectors: GMRES(129) 7.2 ms, 8.1 ms
+    // with one, 9.0 ms in one row)
+    const long nslots = prec == MPMC_FP64 ? ctx->n : ctx->n / 2;   // n = 12 V is even
+    const int Sbig = prec == MPMC_FP64 ? 8 : 4;
+    const int S = (nslots + 256L * Sbig - 1) / (256L * Sbig) >= ctx->num_cu ? Sbig : 2;
+    const int NB = (int)((nslots + 256L * S - 1) / (256L * S));
+    int rows = S == 2 ? (int)((4L * ctx->num_cu + NB - 1) / NB) : 1;
+    rows = std::min(rows, (nv + 3) / 4);
+    rows = std::max(rows, (nv + kDcgsRunMaxV - 1) / kDcgsRunMaxV);
+    const int per = rows > 1 ? ((nv + rows - 1) / rows + 1) / 2 * 2 : std::max(nv, 1);
+    rows = nv > 0 ? (nv + per - 1) / per : 1;
     double2 *part = (double2 *)ws_get(ctx, WS_PARTIAL, (size_t)(2 * nv + 2) * NB * sizeof(double2));
     if (!part) return MPMC_ENOMEM;
-    if (prec == MPMC_FP64)
-        k_dcgs_dots<MPMC_FP64><<<dim3(NB, groups), 256, 0, ctx->stream>>>(V, vstep, nv, u, z, n, part, NB);
-    else
-        k_dcgs_dots<MPMC_FP32><<<dim3(NB, groups), 256, 0, ctx->stream>>>(V, vstep, nv, u, z, n, part, NB);
+    const dim3 grid(NB, rows);
+    if (prec == MPMC_FP64) {
+        if (S == 8) k_dcgs_dots_run<MPMC_FP64, 8><<<grid, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB, per);
+        else k_dcgs_dots_run<MPMC_FP64, 2><<<grid, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB, per);
+    } else {
+        if (S == 4) k_dcgs_dots_run<MPMC_FP32, 4><<<grid, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB, per);
+        else k_dcgs_dots_run<MPMC_FP32, 2><<<grid, 256, 0, ctx->stream>>>(V, vstep, nv, u, z, nslots, part, NB, per);
+    }
     HIP_OR_RET(ctx, hipGetLastError());
     k_dcgs_reduce<<<2 * nv + 2, 256, 0, ctx->stream>>>(part, NB, D);
     HIP_OR_RET(ctx, hipGetLastError());
@@ -585,7 +499,7 @@ __global__ void k_dcgs_init(double *state) {
     state[2] = 0.0;
 }
 
-// The same process with the delayed second projection (see k_dcgs_dots): per
+// The same process with the delayed second projection (see k_dcgs_dots_run): per
 // step the operator on the candidate u, one dot pass, the coefficient kernel,
 // one update pass; after the last step the candidate's delayed projection
 // completes column d-1 and v_d.
@@ -615,15 +529,13 @@ static int arnoldi_run_dcgs2(mpmc_ctx *ctx, const OpDesc &op, void *V, double *H
     return dcgs_launch_update(ctx, op.prec, V, vstep, d, u, nullptr, nullptr, (char *)V + (size_t)d * vstep, C);
 }
 
-// Automatic choice: on small lattices the step is launch-bound and the
-// shorter kernels of plain CGS2 win (8^4: GMRES(129) 9.3 against 11.7 ms);
-// from 16^4 sites on the step is bound by the basis passes and the delayed
-// form wins (24^4 FP32: 217 against 160 ms).
-constexpr long kDelayedGsMinV = 65536;
-
+// The delayed form is the default: two passes over the basis and five launches
+// a step instead of four and nine.  GMRES(33) / GMRES(129) with the roots: 4^4
+// 1.12 / 5.9 ms (plain CGS2 1.44 / 7.8), 8^4 1.24 / 7.2 (1.54 / 9.6), 12^4 2.10 /
+// 18.1 (3.04 / 28.8); GMRES(33) at 16^4 4.5 (7.4).
 int arnoldi_run(mpmc_ctx *ctx, const OpDesc &op, void *V, double *H, int d, double *state, Scratch &S) {
-    const bool plain = ctx->gs_cgs2 == 1 || (ctx->gs_cgs2 < 0 && ctx->V < kDelayedGsMinV);
-    return plain ? arnoldi_run_cgs2(ctx, op, V, H, d, state, S) : arnoldi_run_dcgs2(ctx, op, V, H, d, state, S);
+    return ctx->gs_cgs2 == 1 ? arnoldi_run_cgs2(ctx, op, V, H, d, state, S)
+                             : arnoldi_run_dcgs2(ctx, op, V, H, d, state, S);
 }
 
 MPMC_API int mpmc_set_arnoldi_cgs2(mpmc_ctx *ctx, int on) {

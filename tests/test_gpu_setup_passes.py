@@ -31,3 +31,15 @@ def test_delayed_matches_plain(dims, kappa, d, prec, tol):
     gap = np.abs(np.subtract.outer(r0, r1))
     assert max(gap.min(axis=0).max(), gap.min(axis=1).max()) < tol * np.abs(r1).max()
     assert abs(P[1].relres - P[0].relres) < tol * P[0].relres
+
+
+def test_more_vectors_than_a_row_holds():
+    """260 steps on a lattice whose dot pass runs one row of the grid up to 256
+    vectors: the residual (a norm relative to the start vector's) to 1e-10."""
+    ctx = mpmc.Context((15, 13, 16, 15), 0.2, inputs.gauge_links((15, 13, 16, 15), 0.5, seed=21))
+    P = []
+    for cgs2 in (1, 0):
+        ctx.set_arnoldi_cgs2(cgs2)
+        P.append(ctx.gmres_poly(1, 0x100, 260))
+    assert P[0].d_eff == P[1].d_eff == 260
+    assert abs(P[0].relres - P[1].relres) < 1e-10
