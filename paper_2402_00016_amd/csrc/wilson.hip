@@ -508,10 +508,10 @@ __device__ __forceinline__ void pin_acc(cpx<T> acc[4][3]) {
 // wavefront's first thread with scalar arithmetic.
 template <bool UNI, int ORDER = 0>
 __device__ __forceinline__ bool locate_at(unsigned tile, long V, int N, long &s, int &r,
-                                          const int *__restrict__ order) {
+                                          const int *__restrict__ order, unsigned B = 256u) {
     const unsigned total = (unsigned)(V * N);
     if constexpr (UNI) {
-        const unsigned w0 = tile * 256u + ((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u);
+        const unsigned w0 = tile * B + ((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u);
         if (w0 >= total) return false;
         if constexpr (ORDER == 0) {
             // site-major: a block holds 256/N sites x N right-hand sides
@@ -535,7 +535,7 @@ __device__ __forceinline__ bool locate_at(unsigned tile, long V, int N, long &s,
         // in the blocked order of the site table, all sites of a chunk before
         // the next chunk (needs N % 64 == 0 and V % S == 0)
         constexpr unsigned W = ORDER == 3 ? 16u : 32u, S = 64u / W;
-        const unsigned w0 = tile * 256u + ((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u);
+        const unsigned w0 = tile * B + ((unsigned)__builtin_amdgcn_readfirstlane(threadIdx.x) & ~63u);
         if (w0 >= total) return false;
         const unsigned lane = threadIdx.x & 63u;
         const unsigned wv = w0 >> 6, wpc = (unsigned)V / S;
@@ -543,7 +543,7 @@ __device__ __forceinline__ bool locate_at(unsigned tile, long V, int N, long &s,
         s = (long)order[q];
         r = (int)(ch * W + lane % W);
     } else {
-        const unsigned t = tile * 256u + threadIdx.x;
+        const unsigned t = tile * B + threadIdx.x;
         if (t >= total) return false;
         const unsigned ss = t / (unsigned)N;
         s = (long)ss;
@@ -552,8 +552,9 @@ __device__ __forceinline__ bool locate_at(unsigned tile, long V, int N, long &s,
     return true;
 }
 template <bool UNI, int ORDER = 0>
-__device__ __forceinline__ bool locate(long V, int N, long &s, int &r, const int *__restrict__ order = nullptr) {
-    return locate_at<UNI, ORDER>(xcd_tile(blockIdx.x, gridDim.x), V, N, s, r, order);
+__device__ __forceinline__ bool locate(long V, int N, long &s, int &r, const int *__restrict__ order = nullptr,
+                                       unsigned B = 256u) {
+    return locate_at<UNI, ORDER>(xcd_tile(blockIdx.x, gridDim.x), V, N, s, r, order, B);
 }
 
 struct WOut {
@@ -693,7 +694,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Occ<P, UNI,
     if constexpr (ORDER >= 3 && P != MPMC_FP16S) in.vrs = vec_rsrc<P>(b, V, N);
     long s;
     int r;
-    if (!locate<UNI, ORDER>(V, N, s, r, order)) return;
+    if (!locate<UNI, ORDER>(V, N, s, r, order, blockDim.x)) return;
     wilson_site<P, UNI, ORDER>(in, o, s, r, N);
 }
 
@@ -2334,8 +2335,21 @@ static bool col64_ok(const mpmc_ctx *ctx, int nrhs) {
     const long per_xcd = (wgs / bsz + 7) / 8 * bsz, rounds = (per_xcd * 8 + ctx->num_cu - 1) / ctx->num_cu;
     return bsz >= 8 && wgs * Lt * 4 >= rounds * (Lt + 1) * ctx->num_cu * 3;
 }
+// FP32 column kernel (2x2x2 tiles) by default: where its rounds of one
+// workgroup per compute unit are filled well enough.  A full round takes ~7.5
+// us per t step (and one step more to start), an emptier one hardly less, the
+// blocked kernel 5.3 us per 1,000 sites x 64: 12^4 x 64 (84% of a round) 88
+// against 90 us, fused steps of 17 roots 1.49 against 1.72 ms; 14^4 (two rounds,
+// 67%) 206 / 199 us and 3.43 / 3.77 ms; 10^4 (49%) 68 / 49 us and 1.19 / 0.86
+// ms; 8^4 (25%) 56 / 22 us and 0.99 / 0.39 ms; 4^4 30 / 5.5 us.
+static bool col_fills(const mpmc_ctx *ctx, int nrhs) {
+    const ColArgs a = col_args(ctx, 2);
+    const long bsz = (long)a.bx * a.by * a.bz, wgs = a.ntiles * (nrhs / 64), Lt = ctx->dims[3];
+    const long per_xcd = (wgs / bsz + 7) / 8 * bsz, rounds = (per_xcd * 8 + ctx->num_cu - 1) / ctx->num_cu;
+    return wgs * Lt * 8 >= rounds * (Lt + 1) * ctx->num_cu * 5;
+}
 static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
-    if (col_ok(ctx, nrhs, prec)) return WILSON_COLUMN;
+    if (col_ok(ctx, nrhs, prec) && col_fills(ctx, nrhs)) return WILSON_COLUMN;
     if (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) return WILSON_COLUMN1;
     return prec == MPMC_FP64 ? 4 : 5;
 }
@@ -2365,7 +2379,7 @@ static int wilson_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
 }
 
 // The fused level step takes the column kernel (FP32: 2x2x2 tiles, FP64:
-// 2x2x1) where the shape allows it; otherwise the 64-wide
+// 2x2x1) where the shape allows it and fills its rounds; otherwise the 64-wide
 // blocked order whenever its chunk tiles hold one chunk each (V % 4 == 0),
 // and the site-major order otherwise;
 // a variant set explicitly for (nrhs, prec) with mpmc_tune_set selects its
@@ -2392,8 +2406,9 @@ static int dot_order(const mpmc_ctx *ctx, int nrhs, int prec) {
         return kDotColumn1;
     if (it != ctx->tune_explicit.end() && it->second == WILSON_COLUMNP && col_ok(ctx, nrhs, prec, 4) && nrhs <= 256)
         return kDotColumnP;
-    if (it == ctx->tune_explicit.end() || it->second >= WILSON_COLUMN)
-        if (col_ok(ctx, nrhs, prec) && nrhs <= 256) return kDotColumn;
+    if (it == ctx->tune_explicit.end() ? col_ok(ctx, nrhs, prec) && col_fills(ctx, nrhs)
+                                       : it->second >= WILSON_COLUMN && col_ok(ctx, nrhs, prec))
+        if (nrhs <= 256) return kDotColumn;
     if (ctx->V % 4 != 0) return 0;
     const int o = (it == ctx->tune_explicit.end() || it->second >= WILSON_COLUMN) ? kDotDefaultOrder : it->second >> 1;
     if (o >= 3) return ctx->V % 16 == 0 ? o : 2;
@@ -2410,11 +2425,20 @@ static long dot_tiles_per_chunk(const mpmc_ctx *ctx, int order, int width) {
     return ctx->V * width / 256;
 }
 
+// Threads per workgroup of k_wilson: one wavefront up to 32 of them per compute
+// unit, so that a small batch reaches every compute unit (nine roots: 4^4 x 64
+// FP32 67 -> 50 us, 8^4 x 3 FP64 88 -> 58, 8^4 x 33 166 -> 143, 12^4 x 12 FP64
+// 384 -> 365; 11^4 x 64, 57 per unit, the same either way); four above, which
+// share more neighbours (16^4 x 50 FP32 3.28 ms, 3.34 with one).
+static unsigned wilson_block(const mpmc_ctx *ctx, int nrhs) {
+    return ctx->V * nrhs <= 32L * 64 * ctx->num_cu ? 64u : 256u;
+}
+
 template <int P, int V_>
 static void launch_uniform(mpmc_ctx *ctx, const WIn<P> &in, const WOut &o, int nrhs, unsigned grid) {
     constexpr int ORDER = V_ >> 1;
-    k_wilson<P, (ORDER <= 2), V_ & 1, ORDER><<<grid, 256, 0, ctx->stream>>>(in.b, in.bsc, in.nbr, in.links, o, ctx->V,
-                                                                          nrhs, ctx->site_order);
+    k_wilson<P, (ORDER <= 2), V_ & 1, ORDER><<<grid, wilson_block(ctx, nrhs), 0, ctx->stream>>>(
+        in.b, in.bsc, in.nbr, in.links, o, ctx->V, nrhs, ctx->site_order);
 }
 
 // Single vectors take k_wilson1 on every lattice (with the table's neighbours
@@ -2443,7 +2467,7 @@ static SvGeom sv_geom(const mpmc_ctx *ctx) {
 template <int P>
 static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
     const long work = ctx->V * nrhs;
-    const unsigned grid = grid_for(work, 256);
+    const unsigned grid = grid_for(work, wilson_block(ctx, nrhs));
     WIn<P> in = make_in<P>(ctx, b, nrhs);
     if constexpr (P != MPMC_FP16S) {
         if (nrhs == 1) {
@@ -2508,7 +2532,8 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
         default: launch_uniform<P, 9>(ctx, in, o, nrhs, grid); break;
         }
     } else {
-        k_wilson<P, false><<<grid, 256, 0, ctx->stream>>>(in.b, in.bsc, in.nbr, in.links, o, ctx->V, nrhs, nullptr);
+        k_wilson<P, false><<<grid, wilson_block(ctx, nrhs), 0, ctx->stream>>>(in.b, in.bsc, in.nbr, in.links, o, ctx->V,
+                                                                              nrhs, nullptr);
     }
 }
 
