@@ -2348,8 +2348,15 @@ static bool col_fills(const mpmc_ctx *ctx, int nrhs) {
     const long per_xcd = (wgs / bsz + 7) / 8 * bsz, rounds = (per_xcd * 8 + ctx->num_cu - 1) / ctx->num_cu;
     return wgs * Lt * 8 >= rounds * (Lt + 1) * ctx->num_cu * 5;
 }
+// Up to two rounds of workgroups the 2x2x4 tiles are faster: a wavefront's two
+// sites share a neighbour, and the links' second read costs little while the
+// operand is in the 256 MB memory-side cache for a good part (operator 16^4 x
+// 64 270 -> 237 us, 16^3 32 517 -> 466, 12^4 90 -> 84, polynomials within 2.5%;
+// 24^4, seven rounds, 1.293 against 1.299 ms, polynomial 12.8 against 13.0).
 static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
-    if (col_ok(ctx, nrhs, prec) && col_fills(ctx, nrhs)) return WILSON_COLUMN;
+    if (col_ok(ctx, nrhs, prec) && col_fills(ctx, nrhs))
+        return col_ok(ctx, nrhs, prec, 4) && col_args(ctx, 2).ntiles * (nrhs / 64) <= 2L * ctx->num_cu ? WILSON_COLUMNP
+                                                                                                       : WILSON_COLUMN;
     if (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) return WILSON_COLUMN1;
     return prec == MPMC_FP64 ? 4 : 5;
 }
