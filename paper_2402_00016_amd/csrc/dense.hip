@@ -567,71 +567,119 @@ __global__ __launch_bounds__(256) void k_aberth_init(const double2 *A, int lda, 
     }
 }
 
-// Row sums of Hyman's recurrence for row i of A (in a[], this lane's
-// columns): s = sum_j A(i, j) x_j - z x_i and s' = sum_j A(i, j) x'_j - z x'_i
-// - x_i, over the slots p0 .. Q-1.  Columns below i hold x_j = 0 (not computed
-// yet), so the sums need no mask.
+// Row sums of Hyman's recurrence for a row of A (in a[], this lane's columns)
+// over the columns inserted so far: P = sum_j A(i, j) x_j, P' = sum_j A(i, j)
+// x'_j, over the slots p0 .. Q-1.  Other columns hold x_j = 0, so the sums
+// need no mask.
 template <int G, int Q>
-__device__ __forceinline__ void hyman_row(const zd (&a)[Q], const zd (&x)[Q], const zd (&xp)[Q], int p0, int n, zd z,
-                                          zd xi, zd xpi, zd &s, zd &sp) {
-    s = mk(0.0, 0.0);
-    sp = mk(0.0, 0.0);
+__device__ __forceinline__ void hyman_row(const zd (&a)[Q], const zd (&x)[Q], const zd (&xp)[Q], int p0, int n, zd &P,
+                                          zd &Pp) {
+    P = mk(0.0, 0.0);
+    Pp = mk(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         if (q < p0) continue;    // a constant once the caller's slot loop is unrolled
         if (G * q >= n) break;   // uniform
-        s = s + a[q] * x[q];
-        sp = sp + a[q] * xp[q];
+        P = P + a[q] * x[q];
+        Pp = Pp + a[q] * xp[q];
     }
-    s = group_sum<G>(s) - z * xi;
-    sp = group_sum<G>(sp) - z * xpi - xi;
+    P = group_sum<G>(P);
+    Pp = group_sum<G>(Pp);
 }
+
+// Rows reach the lanes through LDS in chunks of kAberthRows, the next chunk's
+// loads in flight while one is used: a sweep is one chain over the rows, and a
+// row read from memory by its lanes cost that chain an L2 latency each time
+// (112 and 129 rows: 31.8 -> 27.7 us a sweep, 33 rows 8.3 -> 7.2; the rest is
+// the FP64 work of a row, as 32 lanes per root take as long).
+constexpr int kAberthRows = 4;
+static size_t aberth_lds(int n) { return (size_t)(2 * kAberthRows + 1) * n * sizeof(double2); }
 
 template <int G, int Q>
 __global__ __launch_bounds__(256) void k_aberth_sweep(AberthWs w, int n, int t, double tol) {
+    extern __shared__ double2 ab_lds[];   // [2][kAberthRows][n] rows, [n] rsub
+    double2 *rsub = ab_lds + 2 * kAberthRows * n;
     const double2 *zin = w.z + (size_t)(t & 1) * n;
     double2 *zout = w.z + (size_t)((t + 1) & 1) * n;
     const int g = threadIdx.x & (G - 1);
-    const int k = (int)((blockIdx.x * blockDim.x + threadIdx.x) / G);   // the same in all G lanes of the group
-    if (k >= n) return;
+    const int kk = (int)((blockIdx.x * blockDim.x + threadIdx.x) / G);   // the same in all G lanes of the group
+    const int k = kk < n ? kk : n - 1;
     const zd zk = ld(zin, k);
-    if (w.left[t] == 0 || w.conv[k]) {
-        if (g == 0) st(zout, k, zk);
+    if (w.left[t] == 0) {   // uniform
+        if (kk < n && g == 0) st(zout, k, zk);
         return;
     }
-    zd x[Q], xp[Q], a[Q];
+    // every group walks the rows (the barriers are the workgroup's); a frozen
+    // root's or a spare group's result is dropped below
+    const bool frozen = kk >= n || w.conv[k];
+    // chunk c: kAberthRows rows from n-2 - c kAberthRows down, contiguous in memory
+    constexpr int CH = (kAberthRows * G * Q + 255) / 256;
+    double2 stage[CH];
+    auto chunk_load = [&](int c) {
+        const int hi = n - 2 - kAberthRows * c, lo = max(hi - kAberthRows + 1, 0);
+        const int cnt = hi >= 0 ? (hi - lo + 1) * n : 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int j = g + G * q;
-        x[q] = mk(j == n - 1 ? 1.0 : 0.0, 0.0);
-        xp[q] = mk(0.0, 0.0);
-        a[q] = j < n ? ld(w.arow, (long)(n - 1) * n + j) : mk(0.0, 0.0);
-    }
-    zd xi = mk(1.0, 0.0), xpi = mk(0.0, 0.0);   // x_i, x'_i of the current row (uniform)
-    zd rs = ld(w.rsub, n - 1);
+        for (int q = 0; q < CH; ++q) {
+            const int e = (int)threadIdx.x + 256 * q;
+            stage[q] = e < cnt ? w.arow[(long)lo * n + e] : make_double2(0.0, 0.0);
+        }
+    };
+    auto chunk_store = [&](int c) {   // row r of chunk c at [c & 1][r - lo]
+        const int hi = n - 2 - kAberthRows * c, lo = max(hi - kAberthRows + 1, 0);
+        const int cnt = hi >= 0 ? (hi - lo + 1) * n : 0;
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            const int e = (int)threadIdx.x + 256 * q;
+            if (e < cnt) ab_lds[(c & 1) * kAberthRows * n + e] = stage[q];
+        }
+    };
+    chunk_load(0);
+    for (int e = threadIdx.x; e < n; e += 256) rsub[e] = w.rsub[e];
+    chunk_store(0);
+    __syncthreads();
+    chunk_load(1);
+    int c = 0, lo = max(n - 1 - kAberthRows, 0);   // chunk in use and its lowest row
+    zd x[Q], xp[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) x[q] = xp[q] = mk(0.0, 0.0);
+    // x_i, x'_i of the current row i and the row's sums over the columns past
+    // i (all uniform over the group)
+    zd xi = mk(1.0, 0.0), xpi = mk(0.0, 0.0), P = mk(0.0, 0.0), Pp = mk(0.0, 0.0);
+    zd dz = ld(w.arow, (long)(n - 1) * n + n - 1) - zk;   // A(i, i) - z
     int i = n - 1;
-    // Rows in descending order, grouped by the slot QS of their new column
-    // i - 1 (unrolled: every register index is a constant); slots below QS
-    // hold no computed column yet and are neither summed nor loaded.
+    // Rows in descending order: x_{i-1} follows from row i's sums and its
+    // diagonal term alone, while the lanes form row i - 1's sums with x_i
+    // inserted.  Rows are grouped by the slot QS of column i (unrolled: every
+    // register index is a constant); slots below QS hold no column yet and are
+    // neither summed nor loaded.
 #pragma unroll
     for (int QS = Q - 1; QS >= 0; --QS) {
-        for (; i >= 1 && i - 1 >= G * QS; --i) {
-            zd an[Q];   // row i - 1, in flight while row i is summed
-#pragma unroll
-            for (int q = QS; q < Q; ++q) {
-                const int j = g + G * q;
-                an[q] = (G * q < n && j < n) ? ld(w.arow, (long)(i - 1) * n + j) : mk(0.0, 0.0);
+        for (; i >= 1 && i >= G * QS; --i) {
+            if (i - 1 < lo) {   // uniform: the next chunk
+                ++c;
+                lo = max(lo - kAberthRows, 0);
+                chunk_store(c);
+                __syncthreads();
+                chunk_load(c + 1);
             }
-            const zd rsn = ld(w.rsub, i - 1);
-            zd s, sp;
-            hyman_row<G, Q>(a, x, xp, QS, n, zk, xi, xpi, s, sp);
-            xi = rs * s;    // x_{i-1}, x'_{i-1}: the same bits in every lane
-            xpi = rs * sp;
-            const bool own = g == i - 1 - G * QS;
+            const double2 *row = ab_lds + ((c & 1) * kAberthRows + (i - 1 - lo)) * n;   // row i - 1
+            zd a[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (q < QS) continue;
+                const int j = g + G * q;
+                a[q] = j < n ? ld(row, j) : mk(0.0, 0.0);
+            }
+            const zd dzn = ld(row, i - 1) - zk, rs = ld(rsub, i);
+            const bool own = g == i - G * QS;
             x[QS].re = own ? xi.re : x[QS].re;
             x[QS].im = own ? xi.im : x[QS].im;
             xp[QS].re = own ? xpi.re : xp[QS].re;
             xp[QS].im = own ? xpi.im : xp[QS].im;
+            const zd s = P + dz * xi, sp = Pp + (dz * xpi - xi);
+            hyman_row<G, Q>(a, x, xp, QS, n, P, Pp);
+            xi = rs * s;    // x_{i-1}, x'_{i-1}: the same bits in every lane
+            xpi = rs * sp;
             const double mx = fmax(fmax(fabs(xi.re), fabs(xi.im)), fmax(fabs(xpi.re), fabs(xpi.im)));
             if (mx > 0x1p400) {   // a common power-of-two scale leaves f / f' unchanged
 #pragma unroll
@@ -641,14 +689,17 @@ __global__ __launch_bounds__(256) void k_aberth_sweep(AberthWs w, int n, int t, 
                 }
                 xi = 0x1p-400 * xi;
                 xpi = 0x1p-400 * xpi;
+                P = 0x1p-400 * P;
+                Pp = 0x1p-400 * Pp;
             }
-#pragma unroll
-            for (int q = QS; q < Q; ++q) a[q] = an[q];
-            rs = rsn;
+            dz = dzn;
         }
     }
-    zd f, fp;
-    hyman_row<G, Q>(a, x, xp, 0, n, zk, xi, xpi, f, fp);
+    if (frozen) {
+        if (kk < n && g == 0) st(zout, k, zk);
+        return;
+    }
+    const zd f = P + dz * xi, fp = Pp + (dz * xpi - xi);
     const bool flat = fp.re == 0.0 && fp.im == 0.0;
     const zd N = flat ? mk((double)NAN, (double)NAN) : zdiv(f, fp);   // NaN: no Newton step; the QR takes over
     zd S = mk(0.0, 0.0);
@@ -675,11 +726,11 @@ static int aberth_run(mpmc_ctx *ctx, const double2 *A, int lda, int n, const Abe
     // 16 lanes per root up to 128 rows, 32 beyond; at most 8 columns per lane
     const unsigned b16 = (unsigned)((n + 15) / 16), b32 = (unsigned)((n + 7) / 8);
     for (int t = 0; t < AB_SWEEPS; ++t) {
-        if (n <= 32) k_aberth_sweep<16, 2><<<b16, 256, 0, ctx->stream>>>(w, n, t, AB_TOL);
-        else if (n <= 64) k_aberth_sweep<16, 4><<<b16, 256, 0, ctx->stream>>>(w, n, t, AB_TOL);
-        else if (n <= 128) k_aberth_sweep<16, 8><<<b16, 256, 0, ctx->stream>>>(w, n, t, AB_TOL);
-        else if (n <= 160) k_aberth_sweep<32, 5><<<b32, 256, 0, ctx->stream>>>(w, n, t, AB_TOL);
-        else k_aberth_sweep<32, 8><<<b32, 256, 0, ctx->stream>>>(w, n, t, AB_TOL);
+        if (n <= 32) k_aberth_sweep<16, 2><<<b16, 256, aberth_lds(n), ctx->stream>>>(w, n, t, AB_TOL);
+        else if (n <= 64) k_aberth_sweep<16, 4><<<b16, 256, aberth_lds(n), ctx->stream>>>(w, n, t, AB_TOL);
+        else if (n <= 128) k_aberth_sweep<16, 8><<<b16, 256, aberth_lds(n), ctx->stream>>>(w, n, t, AB_TOL);
+        else if (n <= 160) k_aberth_sweep<32, 5><<<b32, 256, aberth_lds(n), ctx->stream>>>(w, n, t, AB_TOL);
+        else k_aberth_sweep<32, 8><<<b32, 256, aberth_lds(n), ctx->stream>>>(w, n, t, AB_TOL);
     }
     HIP_OR_RET(ctx, hipGetLastError());
     return MPMC_OK;
