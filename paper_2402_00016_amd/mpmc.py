@@ -120,7 +120,7 @@ def _check(rc, ctx):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()   # an int: the void * parameters take it without an object of its own
 
 
 def _h(obj):
