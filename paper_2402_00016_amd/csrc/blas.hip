@@ -1074,7 +1074,8 @@ int blas_multi_axpy(mpmc_ctx *ctx, const void *Vb, long vstride, int vN, int nv,
             else launch(P, std::integral_constant<int, 0>());
         } else {
             const std::integral_constant<int, MPMC_FP32> P;
-            if (nv <= 24) with_count<24>(nv, [&](auto NV) { launch(P, NV); });
+            // 25 to 30 vectors of 16^4 x 12: 424 us with the count known, 500 without
+            if (nv <= 32) with_count<32>(nv, [&](auto NV) { launch(P, NV); });
             else launch(P, std::integral_constant<int, 0>());
         }
         HIP_OR_RET(ctx, hipGetLastError());

@@ -75,3 +75,10 @@ def test_gmres_iterates(fields, dims, N, prec, m, tol):
     ref = gmres_iterates(op, B[pick], m)
     err = np.linalg.norm(X - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() < tol
+
+
+@pytest.mark.parametrize("N", [65, 130])
+def test_gmres_iterates_past_the_counted_updates(fields, N):
+    """FP32 updates know the number of vectors up to 32: 36 steps, the bound of
+    28 scaled by the steps."""
+    test_gmres_iterates(fields, LARGE, N, mpmc.FP32, 36, 1.3e-4)
