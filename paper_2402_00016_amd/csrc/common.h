@@ -64,7 +64,7 @@ struct mpmc_ctx {
     // storage precision of the single-vector Arnoldi cycles (mpmc_gmres_poly, mpmc_deflate)
     int setup_prec = MPMC_FP64;
     // their Gram-Schmidt: 0 = CGS2 with the second projection delayed one step, 1 = plain CGS2,
-    // -1 = by lattice size (plain below 16^4 sites)
+    // -1 = the default, as 0
     int gs_cgs2 = -1;
     // projections per inner GMRES step of mpmc_solve / mpmc_solve_batch: 1, 2, or 0 = one for
     // FP32 and FP16S inner cycles, two for FP64 ones

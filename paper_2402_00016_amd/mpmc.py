@@ -742,7 +742,7 @@ class Context:
 
     def set_arnoldi_cgs2(self, on):
         """1: plain CGS2 in the set-up Arnoldi cycles; 0: CGS2 with the second projection delayed;
-        -1 (default): by lattice size."""
+        -1 (default): as 0."""
         _check(_L.mpmc_set_arnoldi_cgs2(self.handle, int(on)), self.handle)
 
     def set_solve_gs_passes(self, passes):
