@@ -389,8 +389,9 @@ int mpmc_solve_batch(mpmc_ctx *const *ctxs, int count, const void *const *b, voi
  *               concurrent workgroups cover twice the sites and fewer
  *               neighbours fall outside them (3.5 reads per site).
  * Defaults: variant 12 or 10 (FP32; lattices whose columns fill the chip, 12
- * up to two rounds of workgroups) or 11 (FP64) where it applies, else 5 for
- * FP32/FP16S and 4 for FP64.
+ * up to two rounds of workgroups) or 11 (FP64) where it applies, else 9 (FP32,
+ * from 16 wavefronts per compute unit on) or 8 (FP64) where V % 16 == 0 and
+ * the vector is at most 256 MB, else 5 for FP32/FP16S and 4 for FP64.
  * mpmc_autotune times every variant on (nrhs, prec) with scratch vectors of
  * the context (2 warm-up + 5 timed launches each, HIP events) and keeps the
  * fastest for all later Wilson launches on ctx with that (nrhs, prec),

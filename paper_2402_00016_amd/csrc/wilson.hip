@@ -2348,6 +2348,19 @@ static bool col_fills(const mpmc_ctx *ctx, int nrhs) {
     const long per_xcd = (wgs / bsz + 7) / 8 * bsz, rounds = (per_xcd * 8 + ctx->num_cu - 1) / ctx->num_cu;
     return wgs * Lt * 8 >= rounds * (Lt + 1) * ctx->num_cu * 5;
 }
+// Where no column kernel runs and the operand fits the 256 MB memory-side
+// cache, 32-wide chunks (two sites per wavefront) beat the 64-wide ones: an
+// XCD then sweeps whole chunks of the lattice.  FP64 x 64: 8^4 42 -> 36 us,
+// 12.12.12.4 70 -> 61, 12^4 205 -> 191; fused levels of nine roots 414 -> 356, 661 ->
+// 557, 1,941 -> 1,730 us.  FP32: 10^4 51 -> 46 us, 7.12.11.8 41 -> 36, levels 466 ->
+// 428, 399 -> 349 us; below 16 wavefronts per compute unit it is even or worse
+// (6.6.6.8 11.8 / 12.5 us).
+static bool narrow_fits(const mpmc_ctx *ctx, int nrhs, int prec) {
+    const long pairs = ctx->V * nrhs;
+    return prec != MPMC_FP16S && ctx->V % 16 == 0 && nrhs % 64 == 0 &&
+           pairs * (prec == MPMC_FP64 ? 192L : 96L) <= 256L << 20 &&
+           (prec == MPMC_FP64 || pairs >= 16L * 64 * ctx->num_cu);
+}
 // Up to two rounds of workgroups the 2x2x4 tiles are faster: a wavefront's two
 // sites share a neighbour, and the links' second read costs little while the
 // operand is in the 256 MB memory-side cache for a good part (operator 16^4 x
@@ -2358,6 +2371,7 @@ static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
         return col_ok(ctx, nrhs, prec, 4) && col_args(ctx, 2).ntiles * (nrhs / 64) <= 2L * ctx->num_cu ? WILSON_COLUMNP
                                                                                                        : WILSON_COLUMN;
     if (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) return WILSON_COLUMN1;
+    if (narrow_fits(ctx, nrhs, prec)) return prec == MPMC_FP64 ? 8 : 9;
     return prec == MPMC_FP64 ? 4 : 5;
 }
 static double link_bytes(int prec) { return prec == MPMC_FP64 ? 576.0 : 288.0; }
@@ -2386,13 +2400,15 @@ static int wilson_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
 }
 
 // The fused level step takes the column kernel (FP32: 2x2x2 tiles, FP64:
-// 2x2x1) where the shape allows it and fills its rounds; otherwise the 64-wide
+// 2x2x1) where the shape allows it and fills its rounds; otherwise the
+// 32-wide blocked order where narrow_fits holds, the 64-wide
 // blocked order whenever its chunk tiles hold one chunk each (V % 4 == 0),
 // and the site-major order otherwise;
 // a variant set explicitly for (nrhs, prec) with mpmc_tune_set selects its
 // traversal (orders 0 and 1: site-major; 3 and 4 need V % 16 == 0), and
 // otherwise mpmc_autotune_level's choice, once made, replaces the default.
 constexpr int kDotDefaultOrder = 2;   // 64-wide blocked chunks (where no column kernel applies)
+constexpr int kDotNarrowOrder = 4;    // 32-wide ones, where narrow_fits says so
 constexpr int kDotColumn = 5;         // order code of the column-streaming fused step (2x2x2 tiles)
 constexpr int kDotColumn1 = 6;        // the same with 2x2x1 tiles (and the FP64 one)
 constexpr int kDotColumnP = 7;        // 2x2x4 tiles, 32-wide chunks (k_wilson_colp)
@@ -2417,7 +2433,9 @@ static int dot_order(const mpmc_ctx *ctx, int nrhs, int prec) {
                                        : it->second >= WILSON_COLUMN && col_ok(ctx, nrhs, prec))
         if (nrhs <= 256) return kDotColumn;
     if (ctx->V % 4 != 0) return 0;
-    const int o = (it == ctx->tune_explicit.end() || it->second >= WILSON_COLUMN) ? kDotDefaultOrder : it->second >> 1;
+    const int o = it == ctx->tune_explicit.end() ? (narrow_fits(ctx, nrhs, prec) ? kDotNarrowOrder : kDotDefaultOrder)
+                  : it->second >= WILSON_COLUMN  ? kDotDefaultOrder
+                                                 : it->second >> 1;
     if (o >= 3) return ctx->V % 16 == 0 ? o : 2;
     return o == 2 ? 2 : 0;
 }

@@ -43,3 +43,18 @@ def test_default_fp32_matches_blocked_and_column(dims, N):
         assert torch.equal(y, ctx.apply_M(x, N, mpmc.FP32))
         X1 = ctx.level(P, None, None, 1, 5, 1, 0, N, prec=mpmc.FP32)[0]
         assert np.linalg.norm(X - X1) < 1e-13 * np.linalg.norm(X1)
+
+
+@pytest.mark.parametrize("prec,wide", [(mpmc.FP64, 4), (mpmc.FP32, 5)])
+@pytest.mark.parametrize("dims,N", [((4, 4, 3, 4), 64), ((7, 8, 9, 8), 64), ((7, 3, 5, 7), 64), ((12, 5, 12, 20), 128)])
+def test_default_chunks_match_wide_ones(dims, N, prec, wide):
+    """Without a column kernel (odd extents): 32- or 64-wide chunks by the
+    operand's size and the number of sites."""
+    ctx = mpmc.Context(dims, 0.12, inputs.gauge_links(dims, 0.5, seed=8))
+    x = ctx.noise(7, 1, 0, N, prec)
+    P = ctx.poly_from_roots(1.0 + 0.4 * np.exp(2j * np.pi * np.arange(5) / 5 + 0.3j))
+    y, X = ctx.apply_poly(P, x, N, prec), ctx.level(P, None, None, 1, 5, 1, 0, N, prec=prec)[0]
+    ctx.tune_set(N, prec, wide)
+    assert torch.equal(y, ctx.apply_poly(P, x, N, prec))
+    X1 = ctx.level(P, None, None, 1, 5, 1, 0, N, prec=prec)[0]
+    assert np.linalg.norm(X - X1) < 1e-13 * np.linalg.norm(X1)
