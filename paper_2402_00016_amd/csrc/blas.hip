@@ -597,17 +597,26 @@ constexpr int kFlatMaxN = 512;
 constexpr size_t kFlatCached = (size_t)640 << 20;   // operands up to here: mostly cached (see blas_multi_dot)
 
 // The flat kernels, or the (site, rhs) tiles?  Tiles read whole lines where 64
-// right-hand sides fill a wavefront: there the dot product gains only from
-// reading w once for more than the tiles' four vectors (24^4 x 64 FP16S: four
-// vectors 1,038 us in tiles and 1,117 us flat, ten 2,805 us and 2,279 us), the
-// update nothing (8^4 x 64, ten vectors: 47 us and 53 us).  Elsewhere the flat
-// kernels win once a vector is too large for its launch to be mere latency
-// (ten vectors and FP32, N = 12: 8^4, 4.7 MB, 15.8 us in tiles and 17.0 us
-// flat; 12^4, 24 MB, 87.7 us and 53.5 us; 16^4, 75 MB, 280 us and 160 us).
+// right-hand sides fill a wavefront: there the update gains nothing flat (8^4 x
+// 64, ten vectors: 47 us and 53 us), the dot product only from reading w once
+// for more than the tiles' four vectors (24^4 x 64 FP16S: four vectors 1,038 us
+// in tiles and 1,117 us flat, ten 2,805 us and 2,279 us), and not on small
+// lattices, where its workgroups and their partial sums cost more than w (whole
+// solves, tiles and flat: 4^4 x 128 FP64 2.75 / 3.10 ms, 4 x 4 x 8 x 8 x 64 5.60 /
+// 5.79, 6^4 x 64 5.20 / 5.21 with restarts of 20 and 8.10 / 7.88 of 50; 4 x 4 x 6
+// x 8 x 256 15.7 / 15.6).  Nor for FP32 and FP64 vectors of 30 to 60 MB once the
+// operands are past kFlatCached: one group of 768 workgroups, whose partial sums
+// take 27 us to add and the tiles' 11 (8^4 x 128 FP32 solve 9.09 / 9.28 ms; 75 MB,
+// 8^4 x 192, 14.36 / 14.18).  Elsewhere the flat kernels win once a vector is too
+// large for its launch to be mere latency (ten vectors and FP32, N = 12: 8^4, 4.7
+// MB, 15.8 us in tiles and 17.0 us flat; 12^4, 24 MB, 87.7 us and 53.5 us; 16^4,
+// 75 MB, 280 us and 160 us).
 bool use_flat(const mpmc_ctx *ctx, int N, int nv, int prec, bool dot) {
     if (N < 2 || N > kFlatMaxN) return false;
-    if (N % 64 == 0) return dot && nv > JB;
-    return vec_bytes(ctx, N, prec) >= (size_t)10000000;
+    const size_t vb = vec_bytes(ctx, N, prec);
+    if (N % 64 != 0) return vb >= (size_t)10000000;
+    if (!dot || nv <= JB || (ctx->V < 1200 && ctx->V * N < 150000)) return false;
+    return prec == MPMC_FP16S || (nv + 1) * vb <= kFlatCached || vb >= (size_t)60000000;
 }
 
 // R near 256 threads' worth, moved to where the fewest lanes of the last
