@@ -580,7 +580,7 @@ __global__ __launch_bounds__(256) void k_arnoldi_finish(const double2 *__restric
     }
 }
 
-// ---- batches of 2 .. 512 right-hand sides with one basis vector per rhs ----
+// ---- batches of 2 .. 512 right-hand sides with one basis vector per rhs (a solution's correction: from 1) ----
 // A vector is a flat array of rows (site, component) of N elements.  A
 // workgroup takes R consecutive rows at a time, R N <= 512 threads, thread t
 // element t of them: its right-hand side t % N never changes, and whatever N
@@ -1148,7 +1148,10 @@ int blas_solution_add(mpmc_ctx *ctx, const void *Vb, size_t vstride_b, int nv, i
                       const double *y_dev) {
     if (nv <= 0) return MPMC_OK;
     const double2 *y = (const double2 *)y_dev;
-    if (prec != MPMC_FP16S && use_flat(ctx, nrhs, nv, prec, false)) {
+    // a single vector is one run of elements: flat, a tile's lanes are 12 elements
+    // apart (20 FP64 vectors of 16^4: 52 us in tiles, 45 us; solves with restarts
+    // of ten at 24^4 21.1 -> 20.7 ms, 8^4 1.44 -> 1.40)
+    if (prec != MPMC_FP16S && (nrhs == 1 || use_flat(ctx, nrhs, nv, prec, false))) {
         const FlatTiling t = flat_tiling(ctx, nrhs, 1);
         auto launch = [&](auto P, auto NV) {
             k_multiaxpy_flat<decltype(P)::value, decltype(NV)::value, true><<<t.NB, t.threads, 0, ctx->stream>>>(
