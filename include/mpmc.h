@@ -388,8 +388,10 @@ int mpmc_solve_batch(mpmc_ctx *const *ctxs, int count, const void *const *b, voi
  *               two sites of a column pair (32 lanes each), so an XCD's
  *               concurrent workgroups cover twice the sites and fewer
  *               neighbours fall outside them (3.5 reads per site).
- * Defaults: variant 12 or 10 (FP32; lattices whose columns fill the chip, 12
- * up to two rounds of workgroups) or 11 (FP64) where it applies, else 9 (FP32,
+ * Defaults: variant 12 or 10 (FP32; lattices whose columns fill the chip; 12
+ * up to two rounds of workgroups, for operator launches where there is a
+ * second round or a larger block of sites per XCD, for the steps of a
+ * polynomial where there are both) or 11 (FP64) where it applies, else 9 (FP32,
  * from 16 wavefronts per compute unit on) or 8 (FP64) where V % 16 == 0 and
  * the vector is at most 256 MB, else 5 for FP32/FP16S and 4 for FP64.
  * mpmc_autotune times every variant on (nrhs, prec) with scratch vectors of

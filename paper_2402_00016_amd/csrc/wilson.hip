@@ -2361,15 +2361,27 @@ static bool narrow_fits(const mpmc_ctx *ctx, int nrhs, int prec) {
            pairs * (prec == MPMC_FP64 ? 192L : 96L) <= 256L << 20 &&
            (prec == MPMC_FP64 || pairs >= 16L * 64 * ctx->num_cu);
 }
-// Up to two rounds of workgroups the 2x2x4 tiles are faster: a wavefront's two
+// 2x2x4 tiles instead, up to two rounds of 2x2x2 workgroups: a wavefront's two
 // sites share a neighbour, and the links' second read costs little while the
-// operand is in the 256 MB memory-side cache for a good part (operator 16^4 x
-// 64 270 -> 237 us, 16^3 32 517 -> 466, 12^4 90 -> 84, polynomials within 2.5%;
-// 24^4, seven rounds, 1.293 against 1.299 ms, polynomial 12.8 against 13.0).
-static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
+// operand is in the 256 MB memory-side cache for a good part.  They gain where
+// an XCD's block of tiles then covers more sites and where there is a second
+// round; a plain operator needs one of the two (16^4 x 64 248 -> 235 us, 16^3 32
+// 481 -> 463, 16.16.8.8 58.7 -> 57.2, 12^4 x 128 164 -> 163; with neither, 12^4 x
+// 64 80.8 / 81.8 and 12.12.12.8 56.6 / 57.6, they lose), a step of a polynomial,
+// with its sum and more operands to the cache, both (nine roots: 16^4 x 64 2,437
+// -> 2,399 us, 16^3 32 4,711 -> 4,629; with one of them 12^4 x 128 1,752 / 1,793,
+// 16.12.8.24 1,619 / 1,656, 8.8.8.16 x 256 1,182 / 1,207).  24^4, seven rounds:
+// 1.293 against 1.299 ms, polynomial 12.8 against 13.0.
+static bool colp_gains(const mpmc_ctx *ctx, int nrhs, bool step) {
+    const ColArgs a = col_args(ctx, 2), p = col_args(ctx, 4);
+    const long wgs = a.ntiles * (nrhs / 64);
+    if (wgs > 2L * ctx->num_cu) return false;
+    const bool second = wgs > ctx->num_cu, larger = 2 * p.bx * p.by * p.bz > a.bx * a.by * a.bz;
+    return step ? second && larger : second || larger;
+}
+static int default_variant(const mpmc_ctx *ctx, int nrhs, int prec, bool step = false) {
     if (col_ok(ctx, nrhs, prec) && col_fills(ctx, nrhs))
-        return col_ok(ctx, nrhs, prec, 4) && col_args(ctx, 2).ntiles * (nrhs / 64) <= 2L * ctx->num_cu ? WILSON_COLUMNP
-                                                                                                       : WILSON_COLUMN;
+        return col_ok(ctx, nrhs, prec, 4) && colp_gains(ctx, nrhs, step) ? WILSON_COLUMNP : WILSON_COLUMN;
     if (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) return WILSON_COLUMN1;
     if (narrow_fits(ctx, nrhs, prec)) return prec == MPMC_FP64 ? 8 : 9;
     return prec == MPMC_FP64 ? 4 : 5;
@@ -2389,9 +2401,9 @@ static WIn<P> make_in(const mpmc_ctx *ctx, const void *b, int nrhs) {
 }
 
 // Kernel variant for (nrhs, prec): pinned or tuned by the autotuner, else the default.
-static int wilson_variant(const mpmc_ctx *ctx, int nrhs, int prec) {
+static int wilson_variant(const mpmc_ctx *ctx, int nrhs, int prec, bool step = false) {
     const auto it = ctx->tune.find(std::make_pair(nrhs, prec));
-    const int v = it == ctx->tune.end() ? default_variant(ctx, nrhs, prec) : it->second;
+    const int v = it == ctx->tune.end() ? default_variant(ctx, nrhs, prec, step) : it->second;
     if (v == WILSON_COLUMN) return col_ok(ctx, nrhs, prec) ? v : (prec == MPMC_FP64 ? 4 : 5);
     if (v == WILSON_COLUMN1)
         return col_ok(ctx, nrhs, prec, 1) || (prec == MPMC_FP64 && col64_ok(ctx, nrhs)) ? v : (prec == MPMC_FP64 ? 4 : 5);
@@ -2510,7 +2522,9 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
         }
     }
     if constexpr (P == MPMC_FP32) {
-        const int cv = nrhs % 64 == 0 && !o.osc ? wilson_variant(ctx, nrhs, P) : -1;
+        // a polynomial's only step (two roots) moves what an operator moves
+        const bool step = (o.a || o.a_is_b) && (o.out || o.ymode != kYInit);
+        const int cv = nrhs % 64 == 0 && !o.osc ? wilson_variant(ctx, nrhs, P, step) : -1;
         if (cv == WILSON_COLUMN) {
             ColArgs ca = col_args(ctx, 2);
             k_wilson_col<0, false, 2><<<col_grid(ca, nrhs), 512, 0, ctx->stream>>>(
