@@ -2466,15 +2466,22 @@ static long dot_tiles_per_chunk(const mpmc_ctx *ctx, int order, int width) {
 // unit, so that a small batch reaches every compute unit (nine roots: 4^4 x 64
 // FP32 67 -> 50 us, 8^4 x 3 FP64 88 -> 58, 8^4 x 33 166 -> 143, 12^4 x 12 FP64
 // 384 -> 365; 11^4 x 64, 57 per unit, the same either way); four above, which
-// share more neighbours (16^4 x 50 FP32 3.28 ms, 3.34 with one).
-static unsigned wilson_block(const mpmc_ctx *ctx, int nrhs) {
-    return ctx->V * nrhs <= 32L * 64 * ctx->num_cu ? 64u : 256u;
+// share more neighbours (16^4 x 50 FP32 3.28 ms, 3.34 with one).  FP16S has the
+// least to wait for: from 11 wavefronts per unit on, four where they fill the
+// units evenly (16^4 x 4, 16 per unit, 21.1 us, 21.6 with one; 12^4 x 12, 15.2,
+// 16.5 / 17.3; 24 per unit 29.8 / 30.5), one where they leave some short (16.16.
+// 16.17 x 4, 17 per unit, 23.6 / 22.9; 24^4 x 1, 20.2, 81.3 / 76.2).
+static unsigned wilson_block(const mpmc_ctx *ctx, int nrhs, int prec) {
+    const long waves = (ctx->V * nrhs + 63) / 64, round = 4L * ctx->num_cu, rest = waves % round;
+    if (waves > 32L * ctx->num_cu) return 256u;
+    const bool even = rest == 0 || rest * 10 > round * 7;
+    return prec == MPMC_FP16S && even && waves >= 11L * ctx->num_cu ? 256u : 64u;
 }
 
 template <int P, int V_>
 static void launch_uniform(mpmc_ctx *ctx, const WIn<P> &in, const WOut &o, int nrhs, unsigned grid) {
     constexpr int ORDER = V_ >> 1;
-    k_wilson<P, (ORDER <= 2), V_ & 1, ORDER><<<grid, wilson_block(ctx, nrhs), 0, ctx->stream>>>(
+    k_wilson<P, (ORDER <= 2), V_ & 1, ORDER><<<grid, wilson_block(ctx, nrhs, P), 0, ctx->stream>>>(
         in.b, in.bsc, in.nbr, in.links, o, ctx->V, nrhs, ctx->site_order);
 }
 
@@ -2504,7 +2511,7 @@ static SvGeom sv_geom(const mpmc_ctx *ctx) {
 template <int P>
 static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
     const long work = ctx->V * nrhs;
-    const unsigned grid = grid_for(work, wilson_block(ctx, nrhs));
+    const unsigned grid = grid_for(work, wilson_block(ctx, nrhs, P));
     WIn<P> in = make_in<P>(ctx, b, nrhs);
     if constexpr (P != MPMC_FP16S) {
         if (nrhs == 1) {
@@ -2571,7 +2578,7 @@ static void launch_w(mpmc_ctx *ctx, const void *b, WOut &o, int nrhs) {
         default: launch_uniform<P, 9>(ctx, in, o, nrhs, grid); break;
         }
     } else {
-        k_wilson<P, false><<<grid, wilson_block(ctx, nrhs), 0, ctx->stream>>>(in.b, in.bsc, in.nbr, in.links, o, ctx->V,
+        k_wilson<P, false><<<grid, wilson_block(ctx, nrhs, P), 0, ctx->stream>>>(in.b, in.bsc, in.nbr, in.links, o, ctx->V,
                                                                               nrhs, nullptr);
     }
 }
