@@ -423,8 +423,11 @@ int mpmc_tune_set(mpmc_ctx *ctx, int nrhs, int prec, int variant);
  * is timed on (nrhs, prec) (2 warm-up + 5 timed steps, HIP events, best of
  * three interleaved rounds) and the fastest is kept for later level
  * estimates on ctx.  Without this call the step takes the column streaming
- * kernel (2x2x2 tiles in FP32, 2x2x1 in FP64) where it applies, else blocked 64-wide chunks
- * (V % 4 == 0), else site-major.  prec FP64 or FP32, nrhs a multiple of 64
+ * kernel (2x2x2 tiles in FP32, 2x2x1 in FP64; nrhs <= 256) where it applies and
+ * its rounds of workgroups fill the chip well enough, else blocked 32-wide
+ * chunks (V % 16 == 0, a vector of at most 256 MB, in FP32 from 16 wavefronts
+ * per compute unit on), else blocked 64-wide chunks (V % 4 == 0), else
+ * site-major.  prec FP64 or FP32, nrhs a multiple of 64
  * (and of 256 above 256).  order_host (may be NULL): the choice; us_host
  * (may be NULL): double[8] microseconds per step by order (0
  * for orders not tried).  Samples are the same up to the grouping of the FP64

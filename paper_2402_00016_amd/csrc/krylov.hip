@@ -722,7 +722,7 @@ static int apply_single_buf(mpmc_ctx *ctx, const std::vector<double> &roots, int
     // Step k forms w_{k+1} = w_k - M w_k / theta_k.  The sum y = sum_k w_k /
     // theta_k takes two terms in every other step, which holds both w_k and
     // w_{k+1} (the first step starts it), and the last step stores no w: the
-    // degree-17 polynomial moves 48 vectors instead of 66.  Same bits as one
+    // polynomial of 17 roots moves 48 vectors instead of 66.  Same bits as one
     // term a step.  Nine roots: 24^4 x 64 FP32 16.0 -> 12.8 ms, FP64 35.6 ->
     // 25.8 ms, 16^4 x 12 FP32 766 -> 643 us, one vector of 16^4 FP64 239 -> 219 us.
     const void *cur = x;

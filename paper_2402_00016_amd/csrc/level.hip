@@ -255,9 +255,11 @@ MPMC_API int mpmc_level_estimate(mpmc_ctx *ctx, const mpmc_poly *upper, const mp
 // polynomial of each term, both on that term's noise) takes its own run of
 // 64-wide chunks on one right-hand-side axis, runs sorted by decreasing degree,
 // so step k of the fused recurrence is one launch over the runs still active.
-// Per (site, rhs) the arithmetic and the order of every sum are those of
-// mpmc_level_estimate; terms with a double polynomial, or shapes without
-// 64-wide chunks or the blocked traversal, go through mpmc_level_estimate.
+// Per (site, rhs) the arithmetic is that of mpmc_level_estimate; the order of
+// every sum too where that takes the blocked 64-wide traversal (other defaults
+// group the FP64 sums over sites differently).  Terms with a double polynomial,
+// or shapes without 64-wide chunks or the blocked traversal, go through
+// mpmc_level_estimate.
 MPMC_API int mpmc_level_estimate_multi(mpmc_ctx *ctx, int nterms, const mpmc_poly *const *upper,
                                        const mpmc_poly *const *lower, const mpmc_defl *defl, int theta,
                                        uint64_t seed, const uint32_t *streams, uint64_t first, int nnoise, int prec,

@@ -2354,7 +2354,11 @@ static bool col_fills(const mpmc_ctx *ctx, int nrhs) {
 // 12.12.12.4 70 -> 61, 12^4 205 -> 191; fused levels of nine roots 414 -> 356, 661 ->
 // 557, 1,941 -> 1,730 us.  FP32: 10^4 51 -> 46 us, 7.12.11.8 41 -> 36, levels 466 ->
 // 428, 399 -> 349 us; below 16 wavefronts per compute unit it is even or worse
-// (6.6.6.8 11.8 / 12.5 us).
+// (6.6.6.8 11.8 / 12.5 us).  Against the 16-wide ones (variant 6, order 3) FP64
+// is not settled: they are slower or even on even extents (12^4 205 us, level
+// 1,859; 12.12.12.4 59 against 61) and faster on uneven ones (7.12.11.8 66
+// against 80 us, level 609 / 720; 9.12.13.16 218 / 244, 1,942 / 2,101), for the
+// autotuners to find.
 static bool narrow_fits(const mpmc_ctx *ctx, int nrhs, int prec) {
     const long pairs = ctx->V * nrhs;
     return prec != MPMC_FP16S && ctx->V % 16 == 0 && nrhs % 64 == 0 &&
@@ -2472,10 +2476,11 @@ static long dot_tiles_per_chunk(const mpmc_ctx *ctx, int order, int width) {
 // 16.5 / 17.3; 24 per unit 29.8 / 30.5), one where they leave some short (16.16.
 // 16.17 x 4, 17 per unit, 23.6 / 22.9; 24^4 x 1, 20.2, 81.3 / 76.2).
 static unsigned wilson_block(const mpmc_ctx *ctx, int nrhs, int prec) {
-    const long waves = (ctx->V * nrhs + 63) / 64, round = 4L * ctx->num_cu, rest = waves % round;
+    const long waves = (ctx->V * nrhs + 63) / 64, round = 4L * ctx->num_cu;
     if (waves > 32L * ctx->num_cu) return 256u;
-    const bool even = rest == 0 || rest * 10 > round * 7;
-    return prec == MPMC_FP16S && even && waves >= 11L * ctx->num_cu ? 256u : 64u;
+    if (prec != MPMC_FP16S || waves < 11L * ctx->num_cu) return 64u;
+    const long rest = waves % round;
+    return rest == 0 || rest * 10 > round * 7 ? 256u : 64u;
 }
 
 template <int P, int V_>
