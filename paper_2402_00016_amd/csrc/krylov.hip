@@ -723,8 +723,8 @@ static int apply_single_buf(mpmc_ctx *ctx, const std::vector<double> &roots, int
     // theta_k takes two terms in every other step, which holds both w_k and
     // w_{k+1} (the first step starts it), and the last step stores no w: the
     // polynomial of 17 roots moves 48 vectors instead of 66.  Same bits as one
-    // term a step.  Nine roots: 24^4 x 64 FP32 16.0 -> 12.8 ms, FP64 35.6 ->
-    // 25.8 ms, 16^4 x 12 FP32 766 -> 643 us, one vector of 16^4 FP64 239 -> 219 us.
+    // term a step.  Nine roots: 24^4 x 64 FP32 16.0 -> 12.8 ms, FP64 (the column
+    // kernel on both sides) 35.6 -> 25.8 ms, 16^4 x 12 FP32 766 -> 643 us, one vector of 16^4 FP64 239 -> 219 us.
     const void *cur = x;
     for (int k = 0; k + 1 < d; ++k) {
         void *nxt = (cur == wa) ? wb : wa;
